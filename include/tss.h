@@ -124,7 +124,9 @@ int tss_cfg_check(const tss_model_cfg* cfg);
 /* Size queries (bytes); 0 when cfg is invalid.  The caller allocates these
  * device buffers (the library allocates none).  Paper: Appendix / Models
  * (weights), Problem Formulation (the workspace of one parallel verification
- * pass), Experiments / Models (the KV cache the underlying method keeps). */
+ * pass), Experiments / Models (the KV cache the underlying method keeps).
+ * tss_kv_bytes counts the pages and, in the TSS_BF16 mode, the buffers of a
+ * prefill pass of min(2048, max_tokens_per_seq) tokens. */
 size_t tss_weights_bytes(const tss_model_cfg* cfg);
 size_t tss_workspace_bytes(const tss_model_cfg* cfg);
 size_t tss_kv_bytes(const tss_model_cfg* cfg, int32_t n_seqs, int32_t max_tokens_per_seq);
@@ -186,7 +188,9 @@ int tss_set_skip_mask(tss_ctx* ctx, int32_t seq, const uint8_t* mask);
 
 /* Appends n context tokens to sequence seq under its skip mask: their K/V are
  * computed and kept for every layer the mask runs.  The tokens go through the
- * decoder in chunks of min(64, rows of one step).  TSS_ECAPACITY past the
+ * decoder in chunks of min(64, rows of one step); in the TSS_BF16 mode more
+ * tokens than one such chunk go through it in passes of up to 2048 tokens,
+ * whose buffers lie in the KV pool.  TSS_ECAPACITY past the
  * sequence's capacity, TSS_ESTATE if an active layer lacks K/V for the
  * committed context.  Paper: Method / Domain-Aware Skip Controller (the same
  * block rule in the target's forward for every token of the request). */
@@ -364,7 +368,8 @@ int tss_profile_read(tss_ctx* ctx, double* total_ms, int64_t* count, int32_t res
  * most 64 consecutive rows of one KV sequence), and for item i the number of
  * workgroups per head its context pages were split among (groups[i]; 1 = no
  * cross-workgroup merge) and its rows (rows[i]).  groups and rows must hold
- * 16 entries.  *n_items = 0 when the step launched no block.  Waits for the
+ * 16 entries (a prefill pass of more rows reports 16 items).
+ * *n_items = 0 when the step launched no attention.  Waits for the
  * context's stream.  Inspection only (tests assert with it which attention
  * path a launch took); no passage of the paper. */
 int tss_get_attn_split(tss_ctx* ctx, int32_t* n_items, int32_t* groups, int32_t* rows);

@@ -223,6 +223,12 @@ WsLayout ws_layout(const tss_model_cfg* c) {
 struct KvLayout {
   int pages_per_seq = 0, n_pages = 0;
   size_t page_table = 0, rope = 0, pages = 0, total = 0;
+  // buffers of a prefill pass of up to prompt_rows tokens (bf16 mode; 0 rows
+  // otherwise), with the pool because they grow with the longest sequence:
+  // residual, projection input (of either norm), q and attention output or
+  // the SwiGLU output, norm partial sums, K-split partial tiles and counters
+  int prompt_rows = 0;
+  size_t p_h = 0, p_x = 0, p_q = 0, p_o = 0, p_act = 0, p_ss = 0, p_parts = 0, p_count = 0, parts_bytes = 0;
 };
 
 KvLayout kv_layout(const tss_model_cfg* c, int n_seqs, int max_tokens) {
@@ -234,6 +240,21 @@ KvLayout kv_layout(const tss_model_cfg* c, int n_seqs, int max_tokens) {
   k.page_table = take((size_t)k.n_pages * 4);
   k.rope = take((size_t)max_tokens * (c->head_dim / 2) * sizeof(float2));
   k.pages = take((size_t)c->n_layers * k.n_pages * 2 * c->n_heads * kPage * c->head_dim * elem_size(c));
+  // a prompt that one small step takes needs no pass
+  if (c->dtype == TSS_BF16 && max_tokens > std::min(kMaxNodes, row_cap(c))) {
+    const size_t d = c->d_model, f = c->ffn_dim;
+    k.prompt_rows = std::min(kPromptRows, round16(max_tokens));
+    const size_t rows = k.prompt_rows;
+    k.p_h = take(rows * d * 4);
+    k.p_x = take(rows * d * 2);
+    k.p_q = take(std::max(align256(rows * d * 4) + rows * d * 2, rows * f * 2));
+    k.p_o = k.p_q + align256(rows * d * 4);
+    k.p_act = k.p_q;  // written after the O projection has read the attention output
+    k.p_ss = take(rows * (d / 16) * 4);
+    k.parts_bytes = std::min(kPromptParts, kMaxKSplit * ((rows + 255) & ~(size_t)255) * ((d + 255) & ~(size_t)255) * 4);
+    k.p_parts = take(k.parts_bytes);
+    k.p_count = take(kPromptCounters * 4);
+  }
   k.total = off;
   return k;
 }
@@ -516,6 +537,8 @@ int tss_create(const tss_model_cfg* cfg, void* hip_stream, void* dev_weights, si
   if (e == hipSuccess) step("stream sync", hipStreamSynchronize(c->stream));
   if (e == hipSuccess) step("attention LDS attribute", init_kernel_attributes());
   if (e == hipSuccess) step("projection LDS attribute", init_gemm_attributes());
+  if (e == hipSuccess) step("tiled projection LDS attribute", init_tile_attributes());
+  if (e == hipSuccess) step("prompt attention LDS attribute", init_prompt_attributes());
   if (e == hipSuccess) step("timing event", hipEventCreate(&c->ev0));
   if (e == hipSuccess) step("timing event", hipEventCreate(&c->ev1));
   if (e != hipSuccess) {
@@ -1071,6 +1094,144 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
   return TSS_OK;
 }
 
+// Enqueues one prefill pass: M prompt tokens of sequence seq (whose mask is
+// c->step's) at positions pos0 .. pos0 + M - 1, on the context's stream.
+// Only their K/V are kept, so the last block that runs ends with its K/V: its
+// attention and MLP feed nothing.
+int enqueue_prompt(tss_ctx* c, int seq, const int32_t* tokens, int M, int pos0) {
+  const tss_model_cfg& cf = c->cfg;
+  const KvLayout& kl = c->kvl;
+  const int L = cf.n_layers, d = cf.d_model, f = cf.ffn_dim, H = cf.n_heads, hd = cf.head_dim;
+  hipStream_t s = c->stream;
+  c->cur_stream = s;
+  c->prof_armed = false;
+  const int first = next_active(c, 0, -1);
+  if (first == L) return TSS_OK;  // every block skipped: no K/V to compute
+  int last = first;
+  for (int l = next_active(c, 0, first); l < L; l = next_active(c, 0, l)) last = l;
+  const int rt = (M + 15) / 16;
+  const int32_t* pt = (const int32_t*)(c->kv + kl.page_table) + (size_t)seq * kl.pages_per_seq;
+  int32_t* counters = (int32_t*)(c->kv + kl.p_count);
+
+  for (int r0 = 0; r0 < M; r0 += kPromptToks) {
+    PromptEmbedArgs a{};
+    const int rows = std::min(kPromptToks, M - r0);
+    a.embed = c->w + c->wl.embed;
+    std::memcpy(a.tok, tokens + r0, (size_t)rows * 4);
+    a.gain = attn_gain_of(c, first);
+    a.h = (float*)(c->kv + kl.p_h);
+    a.xn = c->kv + kl.p_x;
+    a.ss_out = (float*)(c->kv + kl.p_ss);
+    a.ss_stride = d / 16;
+    a.d = d;
+    a.row0 = r0;
+    a.counters = counters;
+    // the report names the pass's last 64-row runs, one workgroup each (none when no attention runs)
+    const int items = (M + 63) / 64;
+    a.attn_split = (int32_t*)(c->ws + c->wsl.attn_split);
+    a.split_items = first == last ? 0 : std::min(items, kAttnMaxItems);
+    a.split_last = M - (items - 1) * 64;
+    ProfScope ps(c, TSS_K_EMBED, -1);
+    HIPCHK(launch_prompt_embed(a, rows, s), "prompt embed");
+    ps.done();
+  }
+
+  GemmArgs base{};
+  base.M = M;
+  base.Mp = rt * 16;
+  base.n_seqs = 1;
+  base.eps = cf.rms_eps;
+  base.norm_dim = d;
+  base.ss_stride = d / 16;
+  base.ksplit = 1;
+  base.pre_n0 = pos0;
+  base.kpart = (float*)(c->kv + kl.p_parts);
+  base.kcount = counters;
+  base.row_on[0] = base.row_on[1] = ~0ull;
+  int ss_parts = d / 16;  // partial sums of h^2 per row that the last producer wrote
+  for (int l = first; l < L; l = next_active(c, 0, l)) {
+    const LayerW& W = c->wl.layers[l];
+    {
+      GemmArgs a = base;
+      a.w = c->w + W.qkv;
+      a.x = c->kv + kl.p_x;
+      a.K = d;
+      a.N = 3 * d;
+      a.nkc = d / c->KC;
+      a.ss_in = (const float*)(c->kv + kl.p_ss);
+      a.ss_nparts = ss_parts;
+      a.q = (float*)(c->kv + kl.p_q);
+      a.kv_pages = c->kv + kl.pages;
+      a.page_table = pt;
+      a.rope = (const float2*)(c->kv + kl.rope);
+      a.layer = l;
+      a.n_pages_pool = kl.n_pages;
+      a.n_heads = H;
+      a.head_dim = hd;
+      a.d = d;
+      ProfScope ps(c, TSS_K_QKV, l);
+      HIPCHK(launch_tile_prompt(EPI_QKV, prompt_tile(EPI_QKV, rt, a.N / 16, a.nkc), a, s), "prompt qkv");
+      ps.done();
+    }
+    if (l == last) break;
+    {
+      PromptAttnArgs a{};
+      a.q = (const float*)(c->kv + kl.p_q);
+      a.kv_pages = c->kv + kl.pages;
+      a.page_table = pt;
+      a.o = c->kv + kl.p_o;
+      a.M = M;
+      a.n0 = pos0;
+      a.layer = l;
+      a.n_pages_pool = kl.n_pages;
+      a.n_heads = H;
+      a.d = d;
+      a.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)hd));
+      ProfScope ps(c, TSS_K_ATTN, l);
+      HIPCHK(launch_prompt_attn(hd, a, s), "prompt attention");
+      ps.done();
+    }
+    auto resid = [&](int kind, size_t w, const void* x, int K, const float* gain) -> int {
+      GemmArgs a = base;
+      a.w = c->w + w;
+      a.x = x;
+      a.K = K;
+      a.N = d;
+      a.nkc = K / c->KC;
+      a.h = (float*)(c->kv + kl.p_h);
+      a.xn = c->kv + kl.p_x;
+      a.g_next[0] = gain;
+      a.ss_out = (float*)(c->kv + kl.p_ss);
+      const TileShape t = prompt_tile(EPI_RESID, rt, a.N / 16, a.nkc, kl.parts_bytes);
+      a.ksplit = t.ks;
+      ss_parts = (a.N / 16 + tile_wave_cols(t) - 1) / tile_wave_cols(t);
+      ProfScope ps(c, kind, l);
+      HIPCHK(launch_tile_prompt(EPI_RESID, t, a, s), "prompt residual projection");
+      ps.done();
+      return TSS_OK;
+    };
+    int r = resid(TSS_K_OPROJ, W.o, c->kv + kl.p_o, d, (const float*)(c->w + W.mlp_norm));
+    if (r) return r;
+    {
+      GemmArgs a = base;
+      a.w = c->w + W.gateup;
+      a.x = c->kv + kl.p_x;
+      a.K = d;
+      a.N = 2 * f;
+      a.nkc = d / c->KC;
+      a.ss_in = (const float*)(c->kv + kl.p_ss);
+      a.ss_nparts = ss_parts;
+      a.act = c->kv + kl.p_act;
+      ProfScope ps(c, TSS_K_GATEUP, l);
+      HIPCHK(launch_tile_prompt(EPI_SWIGLU, prompt_tile(EPI_SWIGLU, rt, a.N / 16, a.nkc), a, s), "prompt gate/up");
+      ps.done();
+    }
+    r = resid(TSS_K_DOWN, W.down, c->kv + kl.p_act, f, attn_gain_of(c, next_active(c, 0, l)));
+    if (r) return r;
+  }
+  return TSS_OK;
+}
+
 // Waits for the step and collects the profiled launch's event times.  The
 // step's outputs (logits, greedy tokens, split report) are in the workspace
 // it ran on, whether it was enqueued now or replayed from a captured graph.
@@ -1468,6 +1629,22 @@ int tss_prefill(tss_ctx* c, int32_t seq, const int32_t* tokens, int32_t n) {
   st.seq[0] = seq;
   st.compact[0] = false;
   st.mask.assign(c->mask[seq].begin(), c->mask[seq].end());
+  if (n > chunk && c->kvl.prompt_rows > 0) {
+    // passes of many rows: equal ones, in whole blocks of 256 rows
+    const int cap = c->kvl.prompt_rows;
+    const int passes = (n + cap - 1) / cap;
+    const int per = std::min(cap, ((n + passes - 1) / passes + 255) / 256 * 256);
+    for (int done = 0; done < n; done += per) {
+      r = enqueue_prompt(c, seq, tokens + done, std::min(per, n - done), c->n_kv[seq] + done);
+      if (r) return r;
+    }
+    r = finish_step(c);
+    if (r) return r;
+    c->n_kv[seq] += n;
+    for (int l = 0; l < L; ++l)
+      if (!c->mask[seq][l]) c->kv_len[seq][l] = c->n_kv[seq];
+    return TSS_OK;
+  }
   for (int done = 0; done < n; done += chunk) {
     const int M = std::min(chunk, n - done);
     StepParams& sp = *c->sp_host;

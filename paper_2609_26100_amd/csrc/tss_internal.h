@@ -74,6 +74,10 @@ constexpr int kAttnPagesPerWG = 64;
 // more than one row tile, see gemm_ksplit)
 constexpr int kMaxKSplit = 4;
 constexpr int kAttnBatchSlots = 2048;
+constexpr int kPromptRows = 2048;  // most prompt tokens of one prefill pass (bf16 mode)
+constexpr int kPromptToks = 512;   // tokens of one embedding launch of a prefill pass (by value)
+constexpr int kPromptCounters = 256;             // K-split arrival counters of a prefill pass
+constexpr size_t kPromptParts = (size_t)16 << 20;  // most bytes of its K-split partial tiles
 
 template <typename T> struct Mode;
 template <> struct Mode<_Float16> {
@@ -203,6 +207,7 @@ struct GemmArgs {
   int32_t pages[kArgPages];  // physical ids of that sequence's first pages
   const float2* rope;      // [max_pos][hd/2] (cos, sin)
   int layer, n_pages_pool, n_heads, head_dim, d;
+  int pre_n0;              // prompt rows (k_tile): position and KV slot of row 0
   // EPI_RESID
   float* h;                // [Mp][N] residual, updated in place
   void* xn;                // [Mp][N] activation planes of h_new * g_next
@@ -295,6 +300,30 @@ struct CompactArgs {
   uint64_t lay_on[kMaxBatch][kMaxLayers / 64];
 };
 
+// A prefill pass: rows r = 0 .. M-1 are the prompt tokens at positions (and KV
+// slots) n0 + r of one sequence.
+struct PromptEmbedArgs {
+  const void* embed;       // [V][d]
+  int32_t tok[kPromptToks];
+  const float* gain;       // gain of the first RMSNorm
+  float* h;                // [M][d]
+  void* xn;                // projection input, act_index order
+  float* ss_out;           // [M][ss_stride]: sums of h^2 over 16-column parts
+  int ss_stride, d, row0;  // row0: row of tok[0]
+  int32_t* counters;       // cleared by the launch of row 0
+  int32_t* attn_split;     // the attention split report, written by the launch of row 0
+  int split_items, split_last;  // its items (64 rows each, the last one split_last rows)
+};
+
+struct PromptAttnArgs {
+  const float* q;          // [M][d] row-major
+  const uint8_t* kv_pages;
+  const int32_t* page_table;  // the sequence's pages
+  void* o;                 // attention output, act_index order
+  int M, n0, layer, n_pages_pool, n_heads, d;
+  float scale_log2;        // log2(e) / sqrt(hd)
+};
+
 // Events bound to the next launch's own dispatch (profiling).  When `start` is
 // set, TSS_LAUNCH issues the kernel through hipExtLaunchKernel, which stamps
 // the two events with the start and end of the kernel's execution, the same
@@ -324,6 +353,19 @@ hipError_t launch_compact(bool bf16, int n_seqs, const CompactArgs& a, hipStream
 const void* embed_kernel(bool bf16);  // kernel symbol, for updating a captured launch
 hipError_t init_kernel_attributes();  // attention
 hipError_t init_gemm_attributes();
+// Block shape of a tiled projection (k_tile): mr x nc tiles of 16 x 16 outputs
+// per workgroup, ks K splits.
+struct TileShape {
+  int mr, nc, ks;
+};
+// column tiles of one wave (a prompt's residual projections write one partial
+// sum of h^2 per row and wave)
+constexpr int tile_wave_cols(const TileShape& t) { return t.mr == 16 ? 4 : 2; }
+hipError_t launch_tile_prompt(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s);
+hipError_t init_tile_attributes();
+hipError_t launch_prompt_embed(const PromptEmbedArgs& a, int rows, hipStream_t s);
+hipError_t launch_prompt_attn(int head_dim, const PromptAttnArgs& a, hipStream_t s);
+hipError_t init_prompt_attributes();
 hipError_t launch_rope_table(float2* tab, int max_pos, int head_dim, float base, hipStream_t s);
 
 // Host runtime pieces of tss_verify_static (tss_static.hip holds the static
@@ -428,6 +470,33 @@ inline int gemm_ksplit(int epi, int mt, int N, int nkc) {
   ks = ks < 1 ? 1 : (ks > kMaxKSplit ? kMaxKSplit : ks);
   while (ks > 1 && nkc / ks < 8) --ks;
   return ks;
+}
+
+// Block shape of a prompt projection of rt row tiles, ct column tiles and nkc K
+// chunks: the one of least estimated time, rounds of 256 workgroups times the
+// chunks of a split times a chunk's time (0.15 us + 2.6 ns per output tile:
+// 16 x 16 tiles 0.82 us, 16 x 8 0.48 us, 8 x 8 0.32 us measured on the 7B
+// shapes), plus 8 us where the residual projections split K.
+// parts_bytes: room for the partial tiles.
+inline TileShape prompt_tile(int epi, int rt, int ct, int nkc, size_t parts_bytes = 0) {
+  constexpr int shapes[][2] = {{16, 16}, {16, 8}, {8, 8}, {8, 6}, {8, 4}};
+  TileShape best{16, 16, 1};
+  float t_best = 1e30f;
+  for (const auto& sh : shapes) {
+    const int blocks = ((rt + sh[0] - 1) / sh[0]) * ((ct + sh[1] - 1) / sh[1]);
+    for (int ks = 1; ks <= (epi == EPI_RESID ? kMaxKSplit : 1); ++ks) {
+      if (ks > 1 && (blocks * ks > kGemmRound || nkc / ks < 16 || blocks > kPromptCounters ||
+                     (size_t)blocks * ks * sh[0] * sh[1] * 1024 > parts_bytes))
+        break;
+      const int rounds = (blocks * ks + kGemmRound - 1) / kGemmRound;
+      const float t = rounds * ((nkc + ks - 1) / ks) * (0.15f + 0.0026f * sh[0] * sh[1]) + (ks > 1 ? 8.f : 0.f);
+      if (t < t_best) {
+        t_best = t;
+        best = TileShape{sh[0], sh[1], ks};
+      }
+    }
+  }
+  return best;
 }
 
 }  // namespace tss

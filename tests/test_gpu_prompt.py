@@ -1,0 +1,102 @@
+"""Prefill passes of many tokens (bf16 mode) at the sizes where their tiling can go wrong: one token past
+what a small step takes, the edges of the 16-, 128- and 256-row blocks, more than one pass, a pass that
+starts inside a page, both head dims, widths that no column block divides, skipped first, middle and last
+blocks, permuted pages.  Each prompt's K/V are judged through the logits of the steps that read them,
+against the oracle and against the same prompt prefilled in calls of at most 64 tokens (the small-step
+path).
+
+Tolerance: the paths share the operands' fp16 roundings except where a sum's rounding tips a stored fp16
+value, so each is off the oracle by fp16's 2^-11 per operand, about sqrt(4 operands x 2 blocks) * 2^-11 =
+1.4e-3 of the logits' norm; 8e-3 allows for the growth through the blocks."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import OracleSequence, verify
+from tests.gpu_common import gpu_verifier, log, oracle_model, prefill_chunked
+
+pytestmark = pytest.mark.gpu
+
+REL = 8e-3
+HD64 = synth.ModelShape("prompt-d320", 91, n_layers=3, d_model=320, n_heads=5, head_dim=64, ffn_dim=672, vocab=416,
+                        dtype="bf16")
+HD128 = synth.ModelShape("prompt-d640", 92, n_layers=3, d_model=640, n_heads=5, head_dim=128, ffn_dim=1056, vocab=416,
+                         dtype="bf16")
+
+
+def _rel(a, b):
+    a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.fixture(scope="module", params=[HD64, HD128], ids=lambda s: s.name)
+def model(request):
+    shape = request.param
+    max_tokens = 2300
+    pages = 2 * ((max_tokens + 15) // 16)
+    order = np.random.default_rng(3).permutation(pages)
+    v = gpu_verifier(shape, random_gains=True, n_seqs=2, max_tokens=max_tokens, max_nodes=64, page_order=order)
+    yield shape, v, oracle_model(shape, random_gains=True)
+    v.close()
+
+
+@pytest.mark.parametrize("lead,n,skip", [(0, 65, []), (0, 127, []), (5, 128, []), (0, 257, []), (37, 300, []),
+                                         (0, 1025, []), (0, 65, [2]), (37, 300, [0]), (37, 300, [1]), (0, 129, [0, 2])])
+def test_prompt_against_oracle_and_small_steps(model, lead, n, skip):
+    shape, v, m = model
+    mask = synth.mask_from_layers(shape.n_layers, skip)
+    toks = synth.context_tokens(shape.vocab, lead + n, stream=n)
+    draft = synth.context_tokens(shape.vocab, 9, stream=n + 1)
+    tree = synth.random_tree(9, stream=n + 2, max_children=3)
+    for s in (0, 1):
+        v.truncate(s, 0)
+        v.set_mask(s, mask)
+        if lead:
+            v.prefill(s, toks[:lead])
+    v.prefill(0, toks[lead:])
+    for i in range(lead, lead + n, 64):
+        v.prefill(1, toks[i:i + 64][:lead + n - i])
+    assert v.length(0) == v.length(1) == lead + n
+    got = []
+    for s in (0, 1):
+        v.verify(s, draft, tree)
+        got.append(v.logits(9))
+    o = OracleSequence(m, mask)
+    prefill_chunked(m, o, toks)
+    want = verify(m, o, draft, tree).logits
+    log(f"{shape.name} lead {lead} n {n} skip {skip}: rel {_rel(got[0], want):.2e} (small steps {_rel(got[1], want):.2e}, "
+        f"between them {_rel(got[0], got[1]):.2e})")
+    assert _rel(got[0], want) <= REL and _rel(got[0], got[1]) <= REL
+    assert _rel(got[0], want) <= 2 * _rel(got[1], want) + 1e-4   # no less exact than the small steps
+    v.check_kv()
+
+
+def test_prompt_of_two_passes_repeats_bit_for_bit(model):
+    shape, v, m = model
+    toks = synth.context_tokens(shape.vocab, 2240, stream=7)
+    draft = synth.context_tokens(shape.vocab, 6, stream=8)
+    v.set_mask(0, None)
+    out = []
+    for _ in range(2):
+        v.truncate(0, 0)
+        v.prefill(0, toks)
+        v.verify(0, draft)
+        out.append(v.logits(6))
+    np.testing.assert_array_equal(out[0], out[1])
+    v.set_mask(1, None)
+    v.truncate(1, 0)
+    for i in range(0, len(toks), 64):
+        v.prefill(1, toks[i:i + 64])
+    v.verify(1, draft)
+    assert _rel(out[0], v.logits(6)) <= REL
+
+
+def test_every_block_skipped_keeps_the_length(model):
+    shape, v, m = model
+    v.truncate(0, 0)
+    v.set_mask(0, np.ones(shape.n_layers, np.uint8))
+    v.prefill(0, synth.context_tokens(shape.vocab, 200, stream=9))
+    assert v.length(0) == 200
+    v.set_mask(0, None)
+    with pytest.raises(Exception, match="lacks K/V"):
+        v.prefill(0, synth.context_tokens(shape.vocab, 100, stream=9))
