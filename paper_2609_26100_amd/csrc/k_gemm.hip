@@ -704,12 +704,20 @@ static hipError_t gemm_attr() {
                              (int)kGemmLdsMax);
 }
 
+// In the fp16 mode steps of six or more row tiles, and the lm_head of five, are
+// k_tile's (step_tiled).
+template <typename T, int MT, int EPI>
+constexpr bool has_gemm() {
+  return sizeof(T) == 4 || EPI != EPI_LOGITS || MT <= 4;
+}
+
 template <typename T, int MT, int NT>
 static hipError_t gemm_attr_mt() {
   hipError_t e = gemm_attr<T, MT, NT, EPI_QKV>();
   if (e == hipSuccess) e = gemm_attr<T, MT, NT, EPI_RESID>();
   if (e == hipSuccess) e = gemm_attr<T, MT, NT < 2 ? 2 : NT, EPI_SWIGLU>();
-  if (e == hipSuccess) e = gemm_attr<T, MT, NT, EPI_LOGITS>();
+  if constexpr (has_gemm<T, MT, EPI_LOGITS>())
+    if (e == hipSuccess) e = gemm_attr<T, MT, NT, EPI_LOGITS>();
   return e;
 }
 
@@ -746,9 +754,6 @@ hipError_t init_gemm_attributes() {
   if (e == hipSuccess) e = gemm_attr_rows<_Float16, 3>();
   if (e == hipSuccess) e = gemm_attr_rows<_Float16, 4>();
   if (e == hipSuccess) e = gemm_attr_rows<_Float16, 5>();
-  if (e == hipSuccess) e = gemm_attr_rows<_Float16, 6>();
-  if (e == hipSuccess) e = gemm_attr_rows<_Float16, 7>();
-  if (e == hipSuccess) e = gemm_attr_rows<_Float16, 8>();
   if (e == hipSuccess) e = gemm_attr_rows<float, 1>();
   if (e == hipSuccess) e = gemm_attr_rows<float, 2>();
   if (e == hipSuccess) e = gemm_attr_rows<float, 3>();
@@ -790,12 +795,14 @@ static hipError_t launch_mt(int epi, const GemmArgs& a, hipStream_t s) {
     case EPI_QKV: return launch_v<T, MT, NT, EPI_QKV>(a, s);
     case EPI_RESID: return launch_v<T, MT, NT, EPI_RESID>(a, s);
     case EPI_SWIGLU: return launch_v<T, MT, NT < 2 ? 2 : NT, EPI_SWIGLU>(a, s);
-    default: return launch_v<T, MT, NT, EPI_LOGITS>(a, s);
+    default:
+      if constexpr (has_gemm<T, MT, EPI_LOGITS>()) return launch_v<T, MT, NT, EPI_LOGITS>(a, s);
+      return hipErrorInvalidValue;
   }
 }
 
-// mt = 16-row tiles of the step's rows (up to 8 in the bf16 mode, 4 in the
-// f32 mode); nt = 16-column tiles per workgroup (gemm_tiles).
+// mt = 16-row tiles of the step's rows (up to 5 in the bf16 mode, 4 in the
+// f32 mode; step_tiled names the others); nt = 16-column tiles per workgroup (gemm_tiles).
 template <typename T, int MT>
 static hipError_t launch_rows(int epi, int nt, const GemmArgs& a, hipStream_t s) {
   switch (nt) {
@@ -834,9 +841,6 @@ hipError_t launch_gemm(bool bf16, int epi, int mt, int nt, const GemmArgs& a, hi
       case 3: return launch_rows<_Float16, 3>(epi, nt, a, s);
       case 4: return launch_rows<_Float16, 4>(epi, nt, a, s);
       case 5: return launch_rows<_Float16, 5>(epi, nt, a, s);
-      case 6: return launch_rows<_Float16, 6>(epi, nt, a, s);
-      case 7: return launch_rows<_Float16, 7>(epi, nt, a, s);
-      case 8: return launch_rows<_Float16, 8>(epi, nt, a, s);
       default: return hipErrorInvalidValue;
     }
   }

@@ -9,33 +9,48 @@ namespace tss {
 // gain of the first RMSNorm the row's sequence meets; ss_out[m][p] = sum of
 // h[m][k]^2 over the 16 columns of part p (the format every projection
 // epilogue writes, so each norm reads d/16 parts whatever produced them).
-// The step's parameters arrive by value and workgroup 0 stores them for the
-// later kernels of the step (this replaces a separate host-to-device copy,
-// which costs as much as a kernel launch).
+// The step's parameters arrive by value and one workgroup more than the rows
+// stores them for the later kernels of the step (this replaces a separate
+// host-to-device copy, which costs as much as a kernel launch; stored by row
+// 0's workgroup before its row they held up the launch).
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed(EmbedArgs a) {
   constexpr int E = 16 / (int)sizeof(T);  // elements of T per 16-byte chunk
   const int m = blockIdx.x;
   const int d = a.d;
-  if (m == 0) {
-    const uint32_t* src = (const uint32_t*)&a.sp;
-    uint32_t* dst = (uint32_t*)a.sp_dev;
-    for (int i = threadIdx.x; i < (int)(sizeof(StepParams) / 4); i += 256) dst[i] = src[i];
+  if (m == a.M) {
+    // one 16-byte load and store per thread: the argument block lies in host
+    // memory, so a loop would pay its round trip once per iteration
+    static_assert(sizeof(StepParams) % 16 == 0 && sizeof(StepParams) <= 256 * 16, "one round");
+    if (threadIdx.x < sizeof(StepParams) / 16) ((uint4*)a.sp_dev)[threadIdx.x] = ((const uint4*)&a.sp)[threadIdx.x];
     // a step whose blocks are all skipped reports no attention items
     if (threadIdx.x == 0) a.attn_split[2 * kAttnMaxItems] = 0;
     // the merges' arrival counters start every step at zero (their last
     // arrivals also reset them; this holds even when another context's step
     // used the same memory in between)
     for (int i = threadIdx.x; i < a.n_counters; i += 256) a.counters[i] = 0;
+    // each row's position and physical KV slot
+    const int r = (int)threadIdx.x - (256 - kMaxRows);
+    if (r >= 0 && r < a.M) {
+      const int sq = a.sp.row_seq[r], nkv = a.sp.seq_nkv[sq];
+      const int slot = nkv + a.sp.seg_slot0[sq] + r - a.sp.seq_row0[sq];
+      a.rows_dev->pos[r] = nkv + a.sp.depth[r];
+      a.rows_dev->phys[r] = a.page_table[a.pt_off[sq] + (slot >> 4)] * kPage + (slot & 15);
+    }
+    return;
   }
-  const float* gain = a.gain[a.sp.row_seq[m]];
+  // the row's segment out of its aligned word: a scalar load, in flight with
+  // the token's (a byte load would be a vector load and a wait of its own)
+  static_assert(offsetof(StepParams, row_seq) % 4 == 0, "row_seq in words");
+  const int seg = (((const uint32_t*)a.sp.row_seq)[m >> 2] >> (8 * (m & 3))) & 0xff;
+  const float* gain = a.gain[seg];
   // Each thread takes whole 16-column parts (up to two; d <= 8192): the
   // row's chunks and the gains of its parts are requested together, and the
   // part's sum of squares needs no exchange between threads.  The row is the
   // token's embedding (T) or a saved residual row (fp32).
   const bool resume = a.src_h != nullptr;
   const int CPP = resume ? 4 : 16 / E;  // 16-byte chunks per part
-  const uint4* row = resume ? (const uint4*)(a.src_h + (size_t)(m - a.sp.seq_row0[a.sp.row_seq[m]]) * d)
+  const uint4* row = resume ? (const uint4*)(a.src_h + (size_t)(m - a.sp.seq_row0[seg]) * d)
                             : (const uint4*)((const T*)a.embed + (size_t)a.sp.tok[m] * d);
   const int nparts = d / 16;
   uint4 raw[2][4];
@@ -263,9 +278,9 @@ const void* embed_kernel(bool bf16) {
 
 hipError_t launch_embed(bool bf16, const EmbedArgs& a, hipStream_t s) {
   if (bf16)
-    TSS_LAUNCH(k_embed<_Float16>, dim3(a.M), dim3(256), 0, s, a);
+    TSS_LAUNCH(k_embed<_Float16>, dim3(a.M + 1), dim3(256), 0, s, a);
   else
-    TSS_LAUNCH(k_embed<float>, dim3(a.M), dim3(256), 0, s, a);
+    TSS_LAUNCH(k_embed<float>, dim3(a.M + 1), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -24,13 +24,19 @@
 //     to the XCDs round robin), so the row blocks that share weight tiles meet
 //     in one L2.
 //
-// Measured on the 7B shapes (fp16 operands, kernel alone): gate/up of 2048 rows
-// 331 us (1115 TFLOP/s with 16 x 16 tiles; a loop of the same MFMAs and LDS
-// reads without loads or barriers runs at 1976), of 1024 rows 199 us, O / down
-// of 1024 rows 53 / 122 us in 8 x 8 tiles.  What is left is the wait of each
-// stage: with every load an L1 hit gate/up of 2048 rows still takes 313 us.  A
-// prompt of 1024 tokens through four blocks and its first step: 9083 us in
-// 64-row steps of k_gemm, 2128 us in one pass.
+// Measured on the 7B shapes: gate/up of 2048 rows 331 us alone (1115 TFLOP/s
+// with 16 x 16 tiles; a loop of the same MFMAs and LDS reads without loads or
+// barriers runs at 1976), Q/K/V of 1024 rows 118 us in 16 x 12 tiles (130 in 16
+// x 16, three quarters of a round), O / down of 1024 rows 53 / 125 us in 8 x 8.
+// A prompt of 1024 tokens through four blocks and its first step: 9083 us in
+// 64-row steps of k_gemm, 1961 us in one pass.  Steps: step_tiled.
+//
+// What bounds the shapes of up to 128 rows is the requests a CU keeps in
+// flight to L2 and HBM: their time is the weights' at about 22-27 bytes per ns
+// and CU plus the activations' at 60, whatever the depth of the ring (6 to 16
+// stages), and loading waves of their own or weights and activations in
+// rings of different depths change it by less than the runs differ (gate/up
+// of 120 rows 44-49 us, Q/K/V 34-37).
 #include "tss_internal.h"
 
 namespace tss {
@@ -94,13 +100,12 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
   constexpr int ROWS = MR * 16;
   static_assert(MR % WM == 0 && NC % WN == 0 && ST >= 2 && ST * PW < 63, "tile shape");
   static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "a wave owns whole gate/up pairs");
-  static_assert(!PRE || TN == tile_wave_cols(TileShape{MR, NC, 1}), "partial sums of a prompt");
+  static_assert(!PRE || EPI != EPI_RESID || TN == tile_wave_cols(TileShape{MR, NC, 1}), "partial sums of a prompt");
   extern __shared__ __align__(16) uint8_t ring[];  // [ST][U KiB]
   __shared__ float s_scale[ROWS];
   __shared__ int s_seq[EPI == EPI_RESID && !PRE ? ROWS : 1];
-  __shared__ int s_slot[EPI == EPI_QKV ? ROWS : 1];
-  __shared__ int s_pos[EPI == EPI_QKV ? ROWS : 1];
-  __shared__ int s_page[EPI == EPI_QKV ? ROWS : 1];
+  __shared__ int s_pos[EPI == EPI_QKV ? ROWS : 1];   // rotary position
+  __shared__ int s_phys[EPI == EPI_QKV ? ROWS : 1];  // pool page * 16 + token of the page
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, r16 = lane & 15, grp = lane >> 4;
@@ -158,48 +163,69 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
       }
     }
   };
+  // Row data of the epilogue and the partial sums of the RMSNorm row scales
+  // are requested before the ring's first loads, behind which they would
+  // otherwise complete: the threads of a row take 16-byte groups of its parts
+  // in turn, up to SQ at a time.
+  constexpr int TH = W * 64;
+  constexpr int TPR = TH >= 4 * ROWS ? 4 : (TH >= 2 * ROWS ? 2 : 1);
+  constexpr int SQ = 32;
+  constexpr bool ROWDATA = EPI == EPI_QKV || (EPI == EPI_RESID && !PRE);
+  static_assert(TH >= ROWS, "a thread per row");
+  const int rl = threadIdx.x / TPR, rsub = threadIdx.x % TPR;
+  const int rrow = min(rt0 * 16 + rl, M - 1);
+  const bool ss_vec = EPI != EPI_RESID && a.ss_nparts % (4 * TPR) == 0 && a.ss_stride % 4 == 0;
+  const int ss_groups = ss_vec ? a.ss_nparts / (4 * TPR) : 0;  // per thread
+  const float* ss_row = EPI != EPI_RESID ? a.ss_in + (size_t)rrow * a.ss_stride : nullptr;
+  float4 sq[EPI != EPI_RESID ? SQ : 1];
+  if constexpr (EPI != EPI_RESID) {
+    if (rl < ROWS) {
+#pragma unroll
+      for (int i = 0; i < SQ; ++i)
+        if (i < ss_groups) sq[i] = *(const float4*)(ss_row + (i * TPR + rsub) * 4);
+    }
+  }
+  int my_seq = 0, my_pos = 0, my_phys = 0;
+  if (ROWDATA && (int)threadIdx.x < ROWS) {
+    const int row = min(rt0 * 16 + (int)threadIdx.x, M - 1);
+    if constexpr (PRE) {
+      my_pos = a.pre_n0 + row;
+      my_phys = a.page_table[my_pos >> 4] * 16 + (my_pos & 15);
+    } else if constexpr (EPI == EPI_QKV) {
+      my_pos = a.rows->pos[row];
+      my_phys = a.rows->phys[row];
+    } else {
+      my_seq = a.n_seqs == 1 ? 0 : a.sp->row_seq[row];
+    }
+  }
 #pragma unroll
   for (int st = 0; st < ST; ++st)
     if (st < n_st) issue(st, st);
-
-  // Row data of the epilogue, while the first stages are on their way.
-  if constexpr (EPI == EPI_QKV || (EPI == EPI_RESID && !PRE)) {
-    for (int r = threadIdx.x; r < ROWS; r += W * 64) {
-      const int row = min(rt0 * 16 + r, M - 1);
-      if constexpr (PRE) {
-        const int slot = a.pre_n0 + row;
-        s_slot[r] = s_pos[r] = slot;
-        s_page[r] = a.page_table[a.pt_off[0] + (slot >> 4)];
-      } else {
-        const int sq = a.n_seqs == 1 ? 0 : a.sp->row_seq[row];
-        if constexpr (EPI == EPI_RESID) s_seq[r] = sq;
-        if constexpr (EPI == EPI_QKV) {
-          const int nkv = a.sp->seq_nkv[sq];
-          const int slot = nkv + a.sp->seg_slot0[sq] + row - a.sp->seq_row0[sq];
-          s_slot[r] = slot;
-          s_pos[r] = nkv + a.sp->depth[row];
-          s_page[r] = a.page_table[a.pt_off[sq] + (slot >> 4)];
-        }
-      }
+  if (ROWDATA && (int)threadIdx.x < ROWS) {
+    if constexpr (EPI == EPI_QKV) {
+      s_pos[threadIdx.x] = my_pos;
+      s_phys[threadIdx.x] = my_phys;
+    } else {
+      s_seq[threadIdx.x] = my_seq;
     }
   }
-  // RMSNorm row scales from the producer's partial sums: four threads per
-  // row, a fixed order.
-  if (EPI != EPI_RESID) {
-    for (int r = threadIdx.x >> 2; r < ROWS; r += W * 16) {
-      const float* p = a.ss_in + (size_t)min(rt0 * 16 + r, M - 1) * a.ss_stride;
+  if constexpr (EPI != EPI_RESID) {
+    if (rl < ROWS) {
       float s = 0.f;
-      if (a.ss_nparts % 16 == 0 && a.ss_stride % 4 == 0) {
-        for (int q = (threadIdx.x & 3) * 4; q < a.ss_nparts; q += 16) {
-          const float4 v = *(const float4*)(p + q);
+      if (ss_vec) {
+#pragma unroll
+        for (int i = 0; i < SQ; ++i)
+          if (i < ss_groups) s += (sq[i].x + sq[i].y) + (sq[i].z + sq[i].w);
+        for (int i = SQ; i < ss_groups; ++i) {
+          const float4 v = *(const float4*)(ss_row + (i * TPR + rsub) * 4);
           s += (v.x + v.y) + (v.z + v.w);
         }
       } else {
-        for (int q = threadIdx.x & 3; q < a.ss_nparts; q += 4) s += p[q];
+        for (int q = rsub; q < a.ss_nparts; q += TPR) s += ss_row[q];
       }
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
-      if ((threadIdx.x & 3) == 0) s_scale[r] = rsqrtf(s / (float)a.norm_dim + a.eps);
+#pragma unroll
+      for (int off = 1; off < TPR; off <<= 1) s += __shfl_xor(s, off);
+      if (rsub == 0) s_scale[rl] = rsqrtf(s / (float)a.norm_dim + a.eps);
     }
   }
 
@@ -291,6 +317,25 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
   };
 
   if constexpr (EPI == EPI_RESID) {
+    // h and the next norm's gain of one row tile; with few tiles per wave they
+    // are requested before the merge of a K split
+    const int N = a.N;
+    constexpr bool EARLY = TM * TN <= 4;
+    float4 h4[EARLY ? TM : 1][TN], g4[EARLY ? TM : 1][TN];
+    auto operands = [&](int t, float4 (&h)[TN], float4 (&g)[TN]) {
+      const int row = min(row_w + t * 16, M - 1);
+      const float* gain = PRE || a.n_seqs == 1 ? a.g_next[0] : a.g_next[s_seq[row_w + t * 16 - rt0 * 16]];
+#pragma unroll
+      for (int n = 0; n < TN; ++n) {
+        const int col = min(ct_w + n, ct_all - 1) * 16 + grp * 4;
+        h[n] = *(const float4*)(a.h + (size_t)row * N + col);
+        g[n] = *(const float4*)(gain + col);
+      }
+    };
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int t = 0; t < TM; ++t) operands(t, h4[t], g4[t]);
+    }
     if (ks > 1) {
       // K split: publish the partial tiles (agent-scope stores, visible to
       // every XCD once acknowledged), count the arrival, and let the last of
@@ -336,31 +381,24 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
     // residual add, the next norm's input h * gain, partial sums of h^2: one
     // per 16 columns in a step (the format every norm of a step reads), one
     // per wave (TN tiles) in a prompt
-    const int N = a.N;
     constexpr int PN = PRE ? TN : 1;
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
       const int row = row_w + t * 16;
       const bool on = row < M && row_on(row);
-      const float* gain = PRE || a.n_seqs == 1 ? a.g_next[0] : a.g_next[s_seq[row - rt0 * 16]];
-      float4 h4[TN], g4[TN];
-#pragma unroll
-      for (int n = 0; n < TN; ++n) {
-        const int col = min(ct_w + n, ct_all - 1) * 16 + grp * 4;
-        h4[n] = *(const float4*)(a.h + (size_t)min(row, M - 1) * N + col);
-        g4[n] = *(const float4*)(gain + col);
-      }
+      const int tt = EARLY ? t : 0;
+      if constexpr (!EARLY) operands(t, h4[0], g4[0]);
       float ss = 0.f;
 #pragma unroll
       for (int n = 0; n < TN; ++n) {
         const int col = (ct_w + n) * 16 + grp * 4;
         const bool st = on && ct_w + n < ct_all;
         const f32x4 y = acc[t][n];
-        const float4 hn = make_float4(h4[n].x + y[0], h4[n].y + y[1], h4[n].z + y[2], h4[n].w + y[3]);
+        const float4 hn = make_float4(h4[tt][n].x + y[0], h4[tt][n].y + y[1], h4[tt][n].z + y[2], h4[tt][n].w + y[3]);
         if (st) {
           *(float4*)(a.h + (size_t)row * N + col) = hn;
           store_act4<_Float16>(a.xn, a.xn_plane, act_index<_Float16>(row, col, N),
-                               make_float4(hn.x * g4[n].x, hn.y * g4[n].y, hn.z * g4[n].z, hn.w * g4[n].w));
+                               make_float4(hn.x * g4[tt][n].x, hn.y * g4[tt][n].y, hn.z * g4[tt][n].z, hn.w * g4[tt][n].w));
           ss += (hn.x * hn.x + hn.y * hn.y) + (hn.z * hn.z + hn.w * hn.w);
         }
         if ((n + 1) % PN == 0) {
@@ -419,10 +457,10 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
         if (sec == 0) {
           *(f32x4*)(a.q + (size_t)row * d + head * HD + dim) = y;
         } else if (row_on(row)) {
-          const int tin = s_slot[rl] & 15;
+          const int tin = s_phys[rl] & 15;
           _Float16* blk =
               (_Float16*)a.kv_pages +
-              ((((size_t)a.layer * a.n_pages_pool + s_page[rl]) * 2 + (sec - 1)) * a.n_heads + head) * (16 * (size_t)HD);
+              ((((size_t)a.layer * a.n_pages_pool + (s_phys[rl] >> 4)) * 2 + (sec - 1)) * a.n_heads + head) * (16 * (size_t)HD);
           if (sec == 1) {
             typedef _Float16 h4 __attribute__((ext_vector_type(4)));
             *(h4*)(blk + tin * HD + dim) = h4{(_Float16)y[0], (_Float16)y[1], (_Float16)y[2], (_Float16)y[3]};
@@ -491,50 +529,82 @@ static hipError_t tile_go(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The block shapes of each projection (kTileShapes): waves, ring and epilogue.
-#define TSS_TILE_SHAPES(F, EPI, PRE)      \
-  F(16, 16, 2, 4, 1, 4, EPI, PRE)         \
-  F(16, 8, 4, 2, 1, 5, EPI, PRE)          \
-  F(8, 8, 2, 4, 2, 4, EPI, PRE)           \
-  F(8, 6, 2, 3, 2, 3, EPI, PRE)           \
-  F(8, 4, 2, 2, 2, 6, EPI, PRE)
+// Block shapes: MR, NC, waves WM x WN, KCH, ST.  Prompts: the large shapes and
+// those of up to 128 rows; steps: exact row tiles for the residual projections
+// (a K split's partial tiles grow with the rows), 6 or 8 for the others.
+#define TSS_TILES_LARGE(F, E, P)  \
+  F(16, 16, 2, 4, 1, 4, E, P)     \
+  F(16, 8, 4, 2, 1, 5, E, P)      \
+  F(8, 8, 2, 4, 2, 4, E, P)
+#define TSS_TILES_QKV(F, E, P)    \
+  F(6, 3, 2, 3, 2, 6, E, P)       \
+  F(6, 4, 2, 2, 2, 6, E, P)       \
+  F(6, 6, 2, 3, 2, 5, E, P)       \
+  F(8, 3, 2, 3, 2, 6, E, P)       \
+  F(8, 4, 2, 2, 2, 5, E, P)       \
+  F(8, 6, 2, 3, 2, 4, E, P)
+#define TSS_TILES_GATEUP(F, E, P) \
+  F(6, 6, 2, 3, 2, 5, E, P)       \
+  F(6, 8, 2, 4, 2, 5, E, P)       \
+  F(6, 10, 2, 5, 2, 4, E, P)      \
+  F(8, 6, 2, 3, 2, 4, E, P)       \
+  F(8, 10, 2, 5, 2, 4, E, P)
+#define TSS_TILES_RESID(F, E, P)  \
+  F(6, 4, 3, 2, 2, 6, E, P)       \
+  F(8, 4, 4, 2, 2, 6, E, P)
 
-template <int EPI>
-static hipError_t tile_prompt(const TileShape& t, const GemmArgs& a, hipStream_t s) {
-#define F(MR, NC, WM, WN, KCH, ST, E, P) \
+#define TSS_TRY(MR, NC, WM, WN, KCH, ST, E, P) \
   if (t.mr == MR && t.nc == NC) return tile_go<MR, NC, WM, WN, KCH, ST, E, P>(a, s);
-  TSS_TILE_SHAPES(F, EPI, true)
-#undef F
+#define TSS_ATTR(MR, NC, WM, WN, KCH, ST, E, P) \
+  if (e == hipSuccess) e = tile_attr<MR, NC, WM, WN, KCH, ST, E, P>();
+
+#define TSS_PROMPT_SHAPES(F)             \
+  TSS_TILES_LARGE(F, EPI_QKV, true)      \
+  F(16, 12, 2, 4, 1, 5, EPI_QKV, true)   \
+  TSS_TILES_QKV(F, EPI_QKV, true)        \
+  TSS_TILES_LARGE(F, EPI_SWIGLU, true)   \
+  F(16, 12, 4, 2, 1, 5, EPI_SWIGLU, true) \
+  TSS_TILES_GATEUP(F, EPI_SWIGLU, true)  \
+  TSS_TILES_LARGE(F, EPI_RESID, true)    \
+  TSS_TILES_RESID(F, EPI_RESID, true)
+#define TSS_STEP_SHAPES(F)               \
+  TSS_TILES_QKV(F, EPI_QKV, false)       \
+  TSS_TILES_GATEUP(F, EPI_SWIGLU, false) \
+  F(8, 8, 2, 4, 2, 4, EPI_SWIGLU, false) \
+  TSS_TILES_RESID(F, EPI_RESID, false)   \
+  F(2, 4, 2, 4, 2, 8, EPI_RESID, false)  \
+  F(3, 4, 3, 2, 2, 8, EPI_RESID, false)  \
+  F(4, 4, 4, 2, 2, 8, EPI_RESID, false)  \
+  F(5, 4, 5, 2, 2, 6, EPI_RESID, false)  \
+  F(7, 4, 7, 2, 2, 6, EPI_RESID, false)  \
+  F(6, 8, 2, 4, 2, 5, EPI_LOGITS, false) \
+  F(8, 8, 2, 4, 2, 4, EPI_LOGITS, false)
+
+hipError_t init_tile_attributes() {
+  hipError_t e = hipSuccess;
+  TSS_PROMPT_SHAPES(TSS_ATTR)
+  TSS_STEP_SHAPES(TSS_ATTR)
+  return e;
+}
+
+static bool split_ok(int epi, const TileShape& t, const GemmArgs& a) {
+  return a.ksplit == t.ks && t.ks >= 1 && t.ks <= kMaxKSplit &&
+         (t.ks == 1 || (epi == EPI_RESID && a.nkc >= t.ks && a.kpart && a.kcount));
+}
+
+#define TSS_TRY_EPI(MR, NC, WM, WN, KCH, ST, E, P) \
+  if (epi == E) TSS_TRY(MR, NC, WM, WN, KCH, ST, E, P)
+hipError_t launch_tile_prompt(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s) {
+  if (!split_ok(epi, t, a) || a.M < 1 || a.M > kPromptRows || a.nkc < 1 || a.N % 16) return hipErrorInvalidValue;
+  TSS_PROMPT_SHAPES(TSS_TRY_EPI)
   return hipErrorInvalidValue;
 }
 
-template <int EPI>
-static hipError_t tile_prompt_attr() {
-  hipError_t e = hipSuccess;
-#define F(MR, NC, WM, WN, KCH, ST, E, P) \
-  if (e == hipSuccess) e = tile_attr<MR, NC, WM, WN, KCH, ST, E, P>();
-  TSS_TILE_SHAPES(F, EPI, true)
-#undef F
-  return e;
-}
-
-hipError_t init_tile_attributes() {
-  hipError_t e = tile_prompt_attr<EPI_QKV>();
-  if (e == hipSuccess) e = tile_prompt_attr<EPI_RESID>();
-  if (e == hipSuccess) e = tile_prompt_attr<EPI_SWIGLU>();
-  return e;
-}
-
-hipError_t launch_tile_prompt(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s) {
-  if (a.ksplit != t.ks || a.M < 1 || a.M > kPromptRows || a.nkc < 1 || a.N % 16 ||
-      (t.ks > 1 && (epi != EPI_RESID || !a.kpart || !a.kcount)))
+hipError_t launch_tile_step(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s) {
+  if (!split_ok(epi, t, a) || a.M < 1 || a.M > kMaxRows || a.M > t.mr * 16 || a.nkc < 1 || a.N % 16)
     return hipErrorInvalidValue;
-  switch (epi) {
-    case EPI_QKV: return tile_prompt<EPI_QKV>(t, a, s);
-    case EPI_RESID: return tile_prompt<EPI_RESID>(t, a, s);
-    case EPI_SWIGLU: return tile_prompt<EPI_SWIGLU>(t, a, s);
-    default: return hipErrorInvalidValue;
-  }
+  TSS_STEP_SHAPES(TSS_TRY_EPI)
+  return hipErrorInvalidValue;
 }
 
 }  // namespace tss

@@ -44,8 +44,8 @@ struct WeightLayout {
 };
 
 struct WsLayout {
-  size_t sp, result, h, xa, xm, ss_a, ss_m, q, o, act, part_o, part_ml, counters, attn_split, kpart, kcount, acount, logits,
-      am_val, am_idx, greedy, total;
+  size_t sp, rows, result, h, xa, xm, ss_a, ss_m, q, o, act, part_o, part_ml, counters, attn_split, kpart, kcount, acount, logits,
+      am_val, am_idx, greedy, kpart_bytes, total;
   int n_counters;
 };
 
@@ -192,6 +192,7 @@ WsLayout ws_layout(const tss_model_cfg* c) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   w.sp = take(sizeof(StepParams));
+  w.rows = take(sizeof(StepRows));
   w.result = take(kMaxSegs * sizeof(Result));
   w.h = take(Mp * d * 4);
   w.xa = take(ap * Mp * d * es);
@@ -211,7 +212,10 @@ WsLayout ws_layout(const tss_model_cfg* c) {
   w.acount = w.kcount + (d / 16) * 4;
   w.n_counters = c->n_heads * kAttnMaxItems + (int)(d / 16) + 1;
   w.attn_split = take((2 * kAttnMaxItems + 1) * 4);
-  w.kpart = take((size_t)kMaxKSplit * d * Mp * 4);  // K-split partial products of the residual projections
+  // K-split partial products of the residual projections (k_tile's blocks are
+  // 64 columns wide)
+  w.kpart_bytes = (size_t)kMaxKSplit * ((d + 63) & ~(size_t)63) * Mp * 4;
+  w.kpart = take(w.kpart_bytes);
   w.logits = take(Mp * v * 4);
   w.am_val = take((v / 16) * Mp * 4);
   w.am_idx = take((v / 16) * Mp * 4);
@@ -877,7 +881,20 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
   base.ksplit = 1;
   base.wide_wgs = 0;
   base.sp = sp_dev;
+  base.rows = (const StepRows*)(ws + c->wsl.rows);
   base.row_on[0] = base.row_on[1] = ~0ull;
+
+  // Q/K/V, gate/up and lm_head, and the residual projections, which may split K
+  auto project = [&](int epi, GemmArgs& a) -> hipError_t {
+    if (step_tiled(c->bf16, epi, mt, a.N)) {
+      const TileShape t = step_tile(epi, mt, a.N / 16, a.nkc, c->wsl.kpart_bytes);
+      a.ksplit = t.ks;
+      return launch_tile_step(epi, t, a, s);
+    }
+    a.ksplit = gemm_ksplit(epi, mt, a.N, a.nkc);
+    a.wide_wgs = gemm_wide_wgs(epi, mt, a.N);
+    return launch_gemm(c->bf16, epi, mt, gemm_tiles(epi, mt, a.N), a, s);
+  };
 
   for (int l = start_layer; l < L; ++l) {
     if (save_prefix && l > 0)
@@ -941,7 +958,7 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       a.head_dim = hd;
       a.d = d;
       ProfScope ps(c, TSS_K_QKV, l);
-      HIPCHK(launch_gemm(c->bf16, EPI_QKV, mt, gemm_tiles(EPI_QKV, mt, a.N), a, s), "qkv gemm");
+      HIPCHK(project(EPI_QKV, a), "qkv gemm");
       ps.done();
     }
     {  // tree attention
@@ -990,10 +1007,9 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       for (int i = 0; i < kMaxSegs; ++i) a.g_next[i] = (const float*)(c->w + W.mlp_norm);
       a.ss_out = (float*)(ws + c->wsl.ss_m);
       ProfScope ps(c, TSS_K_OPROJ, l);
-      a.ksplit = gemm_ksplit(EPI_RESID, mt, a.N, a.nkc);
       a.kpart = (float*)(ws + c->wsl.kpart);
       a.kcount = (int*)(ws + c->wsl.kcount);
-      HIPCHK(launch_gemm(c->bf16, EPI_RESID, mt, gemm_tiles(EPI_RESID, mt, a.N), a, s), "o gemm");
+      HIPCHK(project(EPI_RESID, a), "o gemm");
       ps.done();
     }
     {  // RMSNorm + gate/up + SwiGLU
@@ -1007,9 +1023,8 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       a.ss_in = (const float*)(ws + c->wsl.ss_m);
       a.act = ws + c->wsl.act;
       a.act_plane = plane_f;
-      a.wide_wgs = gemm_wide_wgs(EPI_SWIGLU, mt, a.N);
       ProfScope ps(c, TSS_K_GATEUP, l);
-      HIPCHK(launch_gemm(c->bf16, EPI_SWIGLU, mt, gemm_tiles(EPI_SWIGLU, mt, a.N), a, s), "gate/up gemm");
+      HIPCHK(project(EPI_SWIGLU, a), "gate/up gemm");
       ps.done();
     }
     {  // down projection + residual; next norm input (each sequence's next block, or the final norm)
@@ -1026,10 +1041,9 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       for (int i = 0; i < kMaxSegs; ++i) a.g_next[i] = attn_gain_of(c, i < B ? next_active(c, i, l) : L);
       a.ss_out = (float*)(ws + c->wsl.ss_a);
       ProfScope ps(c, TSS_K_DOWN, l);
-      a.ksplit = gemm_ksplit(EPI_RESID, mt, a.N, a.nkc);
       a.kpart = (float*)(ws + c->wsl.kpart);
       a.kcount = (int*)(ws + c->wsl.kcount);
-      HIPCHK(launch_gemm(c->bf16, EPI_RESID, mt, gemm_tiles(EPI_RESID, mt, a.N), a, s), "down gemm");
+      HIPCHK(project(EPI_RESID, a), "down gemm");
       ps.done();
     }
   }
@@ -1048,7 +1062,7 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       a.am_val = (float*)(ws + c->wsl.am_val);
       a.am_idx = (int32_t*)(ws + c->wsl.am_idx);
       ProfScope ps(c, TSS_K_LMHEAD, -1);
-      HIPCHK(launch_gemm(c->bf16, EPI_LOGITS, mt, gemm_tiles(EPI_LOGITS, mt, a.N), a, s), "lm_head gemm");
+      HIPCHK(project(EPI_LOGITS, a), "lm_head gemm");
       ps.done();
     }
     {
@@ -1279,6 +1293,9 @@ EmbedArgs embed_args(tss_ctx* c, int start_layer, const float* src_h) {
   a.attn_split = (int32_t*)(c->ws + c->wsl.attn_split);
   a.counters = (int32_t*)(c->ws + c->wsl.counters);
   a.n_counters = c->wsl.n_counters;
+  a.rows_dev = (StepRows*)(c->ws + c->wsl.rows);
+  a.page_table = (const int32_t*)(c->kv + c->kvl.page_table);
+  for (int i = 0; i < c->step.n_seqs; ++i) a.pt_off[i] = c->step.seq[i] * c->kvl.pages_per_seq;
   return a;
 }
 

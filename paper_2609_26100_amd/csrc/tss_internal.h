@@ -141,7 +141,7 @@ __device__ __forceinline__ void store_act4(void* base, size_t plane, size_t idx,
 // other and take consecutive draft slots after the context: node j of
 // segment s has slot seq_nkv[s] + seg_slot0[s] + j.  In a plain batch every
 // segment is its own sequence and seg_slot0 is 0.
-struct StepParams {
+struct alignas(16) StepParams {
   int32_t M;                       // rows
   int32_t n_seqs;                  // segments
   int32_t seq_row0[kMaxSegs + 1];  // first row of each segment; seq_row0[n_seqs] = M
@@ -153,6 +153,13 @@ struct StepParams {
   uint8_t row_seq[kMaxRows];       // segment (0 .. n_seqs-1) of the row
   uint8_t seg_slot0[kMaxSegs];     // first draft slot of each segment, after its sequence's context
   uint8_t row_slot0[kMaxRows];     // seg_slot0 of the row's segment
+};
+
+// What the embedding kernel derives from them for the Q/K/V projections, which
+// would otherwise wait for three dependent loads per row.
+struct StepRows {
+  int32_t pos[kMaxRows];           // rotary position of the row
+  int32_t phys[kMaxRows];          // its KV slot in the pool: page * 16 + token of the page
 };
 
 // Position of a row: its sequence's committed length plus its depth.
@@ -194,6 +201,7 @@ struct GemmArgs {
   float* kpart;            // [strips * ksplit][Mp][16 * NT] partial products
   int* kcount;             // [strips] arrivals, zero between launches
   const StepParams* sp;
+  const StepRows* rows;    // k_tile's Q/K/V of a step
   // rows whose segment runs this block (bit r of row_on[r / 64]); the QKV
   // and residual epilogues write nothing for the other rows
   uint64_t row_on[kMaxRows / 64];
@@ -257,13 +265,13 @@ struct AttnArgs {
 };
 
 struct EmbedArgs {
+  StepParams sp;           // this step's parameters (by value) ...
+  StepParams* sp_dev;      // ... copied here for the later kernels of the step
   const void* embed;       // [V][d] T
   // when set, row m starts from a saved residual instead of its token's
   // embedding: src_h[j][d] fp32 with j = m's local node (a step that resumes
   // after blocks every segment shares with the dense verifier)
   const float* src_h;
-  StepParams sp;           // this step's parameters (by value) ...
-  StepParams* sp_dev;      // ... copied here for the later kernels of the step
   const float* gain[kMaxSegs];   // per segment: gain of the first RMSNorm its rows meet
   float* h;                // [Mp][d]
   void* xn;                // [Mp][d] activation planes
@@ -274,6 +282,9 @@ struct EmbedArgs {
   int32_t* attn_split;     // the attention split report (AttnArgs::split_out): its item count is cleared
   int32_t* counters;       // arrival counters of the step's merges (attention, K split), cleared here
   int n_counters;
+  StepRows* rows_dev;      // every row's position and physical KV slot, written here
+  const int32_t* page_table;
+  int32_t pt_off[kMaxSegs];  // each segment's sequence's pages in it
 };
 
 struct AcceptArgs {
@@ -360,8 +371,9 @@ struct TileShape {
 };
 // column tiles of one wave (a prompt's residual projections write one partial
 // sum of h^2 per row and wave)
-constexpr int tile_wave_cols(const TileShape& t) { return t.mr == 16 ? 4 : 2; }
+constexpr int tile_wave_cols(const TileShape& t) { return t.mr == 16 ? 4 : 2; }  // k_tile asserts it
 hipError_t launch_tile_prompt(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s);
+hipError_t launch_tile_step(int epi, const TileShape& t, const GemmArgs& a, hipStream_t s);
 hipError_t init_tile_attributes();
 hipError_t launch_prompt_embed(const PromptEmbedArgs& a, int rows, hipStream_t s);
 hipError_t launch_prompt_attn(int head_dim, const PromptAttnArgs& a, hipStream_t s);
@@ -416,18 +428,16 @@ inline int gemm_wide_wgs(int epi, int mt, int N) {
 // gate/up takes 8 tiles when they fit 256 workgroups (the 60-node tree
 // 5851 -> 5531 us), or blocks of two widths that fill the round exactly
 // (gemm_wide_pairs), and lm_head 8 tiles where 4 would need two rounds.
-// The residual projections with 2-8 row tiles take four- (two-) tile blocks
+// The residual projections with 2-5 row tiles take four-tile blocks
 // over a share of K instead (gemm_ksplit; the partial tiles meet through agent-scope
-// accesses, with no device-scope fence).
+// accesses, with no device-scope fence).  Rows that step_tiled gives to k_tile
+// never get here.
 inline int gemm_tiles(int epi, int mt, int N) {
   if (gemm_wide_pairs(epi, mt, N) > 0) return 2 * gemm_wide_pairs(epi, mt, N);  // blocks of two widths
-  // residual projections with 2-7 row tiles: four-tile blocks over a share of
+  // residual projections with 2-5 row tiles: four-tile blocks over a share of
   // K (gemm_ksplit), so each workgroup re-reads a quarter of the activation
   // tiles that a one-tile block over all of K would
-  if (epi == EPI_RESID && mt >= 2 && mt <= 7 && N % 64 == 0) return 4;
-  // eight row tiles: two-tile blocks (four would spill), split where that
-  // fills the round (7B: 128 strips x 2; 7B 64-mask sweep 16.05 -> 14.97 ms)
-  if (epi == EPI_RESID && mt == 8 && N % 32 == 0 && N / 32 <= 256) return 2;
+  if (epi == EPI_RESID && mt >= 2 && N % 64 == 0) return 4;
   // gate/up with 2-4 row tiles: eight-tile blocks (four pairs) when they fit
   // one round (7B: 172 workgroups instead of 344 in 1.34 rounds; more row
   // tiles would spill)
@@ -457,39 +467,38 @@ inline int gemm_tiles(int epi, int mt, int N) {
   return N % 64 == 0 ? 4 : (N % 32 == 0 ? 2 : 1);
 }
 
-// K splits of a projection launch: the residual projections with 2-7 row
+// K splits of a projection launch: the residual projections with 2-5 row
 // tiles split K so that their four-tile blocks still fill about one round of
-// 256 workgroups (7B: 64 strips x 4, 13B: 80 x 3, 33B: 104 x 2), and with 8
-// row tiles their two-tile blocks (7B: 128 x 2), each split keeping at least
-// one chunk per wave.  nkc = K chunks of the matrix.
+// 256 workgroups (33B: 104 strips x 2), each split keeping at least one chunk
+// per wave.  nkc = K chunks of the matrix.
 inline int gemm_ksplit(int epi, int mt, int N, int nkc) {
-  const bool four = epi == EPI_RESID && mt >= 2 && mt <= 7 && N % 64 == 0;
-  const bool two = epi == EPI_RESID && mt == 8 && N % 32 == 0 && N / 32 <= 256;
-  if (!four && !two) return 1;
-  int ks = 256 / (N / (four ? 64 : 32));
+  if (epi != EPI_RESID || mt < 2 || N % 64) return 1;
+  int ks = 256 / (N / 64);
   ks = ks < 1 ? 1 : (ks > kMaxKSplit ? kMaxKSplit : ks);
   while (ks > 1 && nkc / ks < 8) --ks;
   return ks;
 }
 
-// Block shape of a prompt projection of rt row tiles, ct column tiles and nkc K
-// chunks: the one of least estimated time, rounds of 256 workgroups times the
-// chunks of a split times a chunk's time (0.15 us + 2.6 ns per output tile:
-// 16 x 16 tiles 0.82 us, 16 x 8 0.48 us, 8 x 8 0.32 us measured on the 7B
-// shapes), plus 8 us where the residual projections split K.
-// parts_bytes: room for the partial tiles.
-inline TileShape prompt_tile(int epi, int rt, int ct, int nkc, size_t parts_bytes = 0) {
-  constexpr int shapes[][2] = {{16, 16}, {16, 8}, {8, 8}, {8, 6}, {8, 4}};
-  TileShape best{16, 16, 1};
+// The cheapest of a projection's block shapes (pairs of MR, NC) for rt row
+// tiles, ct column tiles and nkc K chunks: the one of least estimated time,
+// rounds of 256 workgroups times the chunks of a K split times a chunk's time
+// (0.2 us + 2.7 ns per output tile; measured on the 7B shapes 16 x 16 tiles
+// 0.87-1.0 us, 16 x 12 0.83, 16 x 8 0.53, 8 x 8 0.33, 8 x 6 0.38), plus 8 us
+// where the residual projections split K (parts_bytes: room for the partial
+// tiles).
+template <int NS>
+inline TileShape cheapest_tile(const int (&shapes)[NS][2], int epi, int rt, int ct, int nkc, size_t parts_bytes,
+                               int max_blocks) {
+  TileShape best{shapes[0][0], shapes[0][1], 1};
   float t_best = 1e30f;
   for (const auto& sh : shapes) {
     const int blocks = ((rt + sh[0] - 1) / sh[0]) * ((ct + sh[1] - 1) / sh[1]);
     for (int ks = 1; ks <= (epi == EPI_RESID ? kMaxKSplit : 1); ++ks) {
-      if (ks > 1 && (blocks * ks > kGemmRound || nkc / ks < 16 || blocks > kPromptCounters ||
+      if (ks > 1 && (blocks * ks > kGemmRound || nkc / ks < 16 || blocks > max_blocks ||
                      (size_t)blocks * ks * sh[0] * sh[1] * 1024 > parts_bytes))
         break;
       const int rounds = (blocks * ks + kGemmRound - 1) / kGemmRound;
-      const float t = rounds * ((nkc + ks - 1) / ks) * (0.15f + 0.0026f * sh[0] * sh[1]) + (ks > 1 ? 8.f : 0.f);
+      const float t = rounds * ((nkc + ks - 1) / ks) * (0.2f + 0.0027f * sh[0] * sh[1]) + (ks > 1 ? 8.f : 0.f);
       if (t < t_best) {
         t_best = t;
         best = TileShape{sh[0], sh[1], ks};
@@ -497,6 +506,50 @@ inline TileShape prompt_tile(int epi, int rt, int ct, int nkc, size_t parts_byte
     }
   }
   return best;
+}
+
+// Block shape of a prompt projection.  Up to 128 rows one row block takes all
+// of them, as in a step.
+inline TileShape prompt_tile(int epi, int rt, int ct, int nkc, size_t parts_bytes = 0) {
+  constexpr int q6[][2] = {{6, 3}, {6, 4}, {6, 6}}, q8[][2] = {{8, 3}, {8, 4}, {8, 6}, {8, 8}};
+  constexpr int g6[][2] = {{6, 6}, {6, 8}, {6, 10}}, g8[][2] = {{8, 6}, {8, 8}, {8, 10}};
+  constexpr int r6[][2] = {{6, 4}}, r8[][2] = {{8, 4}};
+  constexpr int wide[][2] = {{16, 16}, {16, 12}, {16, 8}, {8, 8}};
+  constexpr int resid[][2] = {{16, 16}, {16, 8}, {8, 8}, {8, 4}};
+  auto pick = [&](const auto& sh) { return cheapest_tile(sh, epi, rt, ct, nkc, parts_bytes, kPromptCounters); };
+  if (rt > 8) return epi == EPI_RESID ? pick(resid) : pick(wide);
+  if (epi == EPI_QKV) return rt <= 6 ? pick(q6) : pick(q8);
+  if (epi == EPI_SWIGLU) return rt <= 6 ? pick(g6) : pick(g8);
+  return rt <= 6 ? pick(r6) : pick(r8);
+}
+
+// Step projections that k_tile runs (bf16 mode; the others are k_gemm's).
+// What k_gemm's many-row blocks lose to re-reading activations in every wave
+// grows with the rows, and its residual projections sum their waves' partial
+// tiles through LDS before the K split's merge.  In the traced step (us,
+// k_gemm / k_tile): O and down of the 7B shape 13 + 22 / 12 + 21 at 2 row
+// tiles, 16 + 27 / 14 + 26 at 4, 19 + 38 / 18 + 35 at 8, of the 13B shape 21 +
+// 37 / 18 + 39 at 5; with only two K splits (33B) 23 + 49 / 25 + 57 at 3, so
+// those stay up to 5.  8 row tiles: gate/up 69 / 49, Q/K/V 39 / 37, lm_head
+// 89 / 61; 4: 37 / 37, 28 / 27, 53 / 52.  At 5 (13B) lm_head gains (82 / 68) and
+// Q/K/V (40 / 40) and the two-width gate/up (57 / 58) do not.
+inline bool step_tiled(bool bf16, int epi, int rt, int N) {
+  if (!bf16 || rt < 2) return false;
+  if (rt >= 6) return true;
+  if (epi == EPI_RESID) return (N + 63) / 64 * 3 <= kGemmRound;
+  return rt == 5 && (epi == EPI_LOGITS || (epi == EPI_SWIGLU && gemm_wide_pairs(epi, rt, N) == 0));
+}
+
+// Block shape of a step projection that k_tile runs.
+inline TileShape step_tile(int epi, int rt, int ct, int nkc, size_t parts_bytes = 0) {
+  constexpr int q6[][2] = {{6, 3}, {6, 4}, {6, 6}}, q8[][2] = {{8, 3}, {8, 4}, {8, 6}};
+  constexpr int g6[][2] = {{6, 6}, {6, 8}, {6, 10}}, g8[][2] = {{8, 6}, {8, 8}, {8, 10}};
+  auto pick = [&](const auto& sh) { return cheapest_tile(sh, epi, rt, ct, nkc, parts_bytes, ct); };
+  if (epi == EPI_LOGITS) return TileShape{rt <= 6 ? 6 : 8, 8, 1};
+  if (epi == EPI_QKV) return rt <= 6 ? pick(q6) : pick(q8);
+  if (epi == EPI_SWIGLU) return rt <= 6 ? pick(g6) : pick(g8);
+  const int r[][2] = {{rt, 4}};
+  return pick(r);
 }
 
 }  // namespace tss

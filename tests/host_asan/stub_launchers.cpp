@@ -14,6 +14,7 @@ const void* embed_kernel(bool) { return nullptr; }
 hipError_t init_kernel_attributes() { return hipErrorInvalidValue; }
 hipError_t init_gemm_attributes() { return hipErrorInvalidValue; }
 hipError_t launch_tile_prompt(int, const TileShape&, const GemmArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_tile_step(int, const TileShape&, const GemmArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t init_tile_attributes() { return hipErrorInvalidValue; }
 hipError_t launch_prompt_embed(const PromptEmbedArgs&, int, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_prompt_attn(int, const PromptAttnArgs&, hipStream_t) { return hipErrorInvalidValue; }

@@ -1,0 +1,81 @@
+"""Steps of 2 to 8 row tiles (bf16 mode) at the edges of the tiled projections: the first and last row counts
+of a row tile, column counts that no block width divides, an odd number of K chunks, K split unevenly, one
+segment and several, blocks that only some segments run.  Every sequence of a batch is compared with its own
+verify (at most 16 rows: another kernel) and with the oracle.
+
+Tolerance: as for prompts, the operands' fp16 roundings give each path about 1.4e-3 of the logits' norm
+against the oracle; 8e-3 allows for the growth through the blocks."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import OracleSequence, prefill, verify
+from tests.gpu_common import gpu_verifier, log, oracle_model
+
+pytestmark = pytest.mark.gpu
+
+REL = 8e-3
+SMALL = synth.ModelShape("rows-d320", 93, n_layers=2, d_model=320, n_heads=5, head_dim=64, ffn_dim=672, vocab=416,
+                         dtype="bf16")
+SPLIT = synth.ModelShape("rows-d1024", 94, n_layers=2, d_model=1024, n_heads=8, head_dim=128, ffn_dim=2080, vocab=1056,
+                         dtype="bf16")
+
+
+def _rel(a, b):
+    a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.fixture(scope="module", params=[SMALL, SPLIT], ids=lambda s: s.name)
+def model(request):
+    shape = request.param
+    order = np.random.default_rng(5).permutation(8 * 13)
+    v = gpu_verifier(shape, random_gains=True, n_seqs=8, max_tokens=200, max_nodes=64, max_batch=8, page_order=order)
+    m = oracle_model(shape, random_gains=True)
+    masks = [synth.mask_from_layers(2, [] if i % 3 == 0 else [i % 2]) for i in range(8)]
+    oseqs = []
+    for i in range(8):
+        ctx = synth.context_tokens(shape.vocab, 20 + 7 * i, stream=300 + i)
+        v.set_mask(i, masks[i])
+        v.prefill(i, ctx)
+        o = OracleSequence(m, masks[i])
+        prefill(m, o, ctx)
+        oseqs.append(o)
+    yield shape, v, m, oseqs
+    v.close()
+
+
+# nodes per sequence; 17, 32, 33, 48, 64, 65, 80, 81, 96, 97, 112, 113 and 128 rows
+@pytest.mark.parametrize("nodes", [[9, 8], [16, 16], [16, 16, 1], [12] * 4, [8] * 8, [16] * 4 + [1], [10] * 8,
+                                   [16] * 5 + [1], [16] * 6, [13] * 7 + [6], [14] * 8, [16] * 7 + [1], [16] * 8],
+                         ids=lambda n: str(sum(n)))
+def test_batch_rows_against_single_verifies_and_oracle(model, nodes):
+    shape, v, m, oseqs = model
+    seqs = list(range(len(nodes)))
+    drafts = [synth.context_tokens(shape.vocab, n, stream=400 + 10 * i + n) for i, n in enumerate(nodes)]
+    parents = [synth.random_tree(n, stream=500 + i, max_children=3) if i % 2 else None for i, n in enumerate(nodes)]
+    v.verify_batch(seqs, drafts, parents)
+    got = v.logits(sum(nodes))
+    single, want = [], []
+    for i in seqs:
+        v.verify(i, drafts[i], parents[i])
+        single.append(v.logits(nodes[i]))
+        want.append(verify(m, oseqs[i], drafts[i], parents[i]).logits)
+    single, want = np.concatenate(single), np.concatenate(want)
+    e, e1 = _rel(got, want), _rel(single, want)
+    log(f"{shape.name} {sum(nodes)} rows: rel {e:.2e} (singles {e1:.2e}, between them {_rel(got, single):.2e})")
+    assert e <= REL and _rel(got, single) <= REL and e <= 2 * e1 + 1e-4
+    # a repeat gives the same bits
+    v.verify_batch(seqs, drafts, parents)
+    np.testing.assert_array_equal(v.logits(sum(nodes)), got)
+
+
+@pytest.mark.parametrize("n", [17, 33, 64])
+def test_one_tree_of_many_rows(model, n):
+    shape, v, m, oseqs = model
+    tok = synth.context_tokens(shape.vocab, n, stream=600 + n)
+    par = synth.random_tree(n, stream=600 + n, max_children=4)
+    v.verify(3, tok, par)
+    e = _rel(v.logits(n), verify(m, oseqs[3], tok, par).logits)
+    log(f"{shape.name} tree of {n}: rel {e:.2e}")
+    assert e <= REL
