@@ -27,6 +27,9 @@
 //   * Operands: fp16 K/V pages, q and probabilities with fp32 accumulation
 //     (v_mfma_f32_16x16x32_f16 for S, v_mfma_f32_16x16x16_f16 for P V) in the
 //     bf16 mode; fp32 throughout (v_mfma_f32_16x16x4_f32) in the f32 mode.
+// Items of several row tiles in launches over one KV sequence take another
+// kernel in the bf16 mode (k_attn_tree below).
+//
 // The 8 waves' softmax states meet in LDS (fixed order), tile after tile.
 // With G = 1 the workgroup writes the normalised rows itself.  With G > 1,
 // in launches of single-tile items, each workgroup writes its partial states
@@ -613,20 +616,280 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(AttnArgs a) {
   if (threadIdx.x == 0) a.counters[ctr] = 0;
 }
 
+// Items of several row tiles in the bf16 mode over one KV sequence: eight waves
+// share every page instead of walking pages of their own.  A step is four
+// pages (64 tokens), brought into an LDS ring by global -> LDS loads, the K or
+// V block of one page per wave; wave w then applies two of the four pages to
+// one row tile (with one wave for all four pages a step took 2 us, longer than
+// its loads).  Workgroup g of the item takes steps g, g + groups, ...; the
+// first kTreeStages of them are requested before anything else where their
+// page ids are arguments (every argument id names a page of the pool, so the
+// loads are in bounds even past the context).  The two waves of a tile meet in
+// LDS at the end, lane by lane (walking pages of their own, eight waves had
+// four tiles each to merge there, which took longer than the walk), and the
+// tile's state is left to the merge launch.  The scores and outputs are laid
+// out as in the prompt kernel: a lane holds one query row.  Measured (traced,
+// k_attn / this): 61 rows at 2048 tokens (7B) 23.4 / 16.5 us, 33 rows at 4096
+// (33B) 34.2 / 27.3, two items of 60 rows at 512 (7B) 20.7 / 12.1.
+constexpr int kTreeWaves = 8, kTreePages = 4, kTreeStages = 4;
+template <int HD>
+constexpr size_t tree_lds() { return (size_t)kTreeStages * kTreePages * HD * 64; }
+__device__ __forceinline__ int tree_steps(int n_pages) { return (n_pages + kTreePages - 1) / kTreePages; }
+// Workgroups of an item, each leaving one partial state.
+__device__ __forceinline__ int tree_groups(const AttnArgs& a, int n_pages) {
+  return min(a.groups, tree_steps(n_pages));
+}
+
+template <int HD>
+__global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
+  constexpr int NK = HD / 32;              // KiB of a K (or V) page block
+  constexpr int PW = NK;                   // loads of one wave per step: half a page
+  constexpr int STAGE = kTreePages * 2 * NK * 1024;
+  static_assert(kTreeStages * PW <= 63, "counted waits");
+  extern __shared__ __align__(16) uint8_t tree_ring[];
+  const int head = blockIdx.x, y = blockIdx.y, g = blockIdx.z;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r16 = lane & 15, grp = lane >> 4;
+  const int row0 = a.item_row0[y], Ms = a.item_rows[y], T = (Ms + 15) >> 4;
+  const int stride = a.groups;             // steps between a workgroup's steps
+  // read ahead of the page loads, as a scalar: a vector load's wait would cover them
+  const int sq = a.item_seg[y];
+  const int n_kv = a.sp->seq_nkv[sq];
+
+  const size_t blk = 16 * (size_t)HD * 2;  // bytes of a page's K block of one head
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)tree_ring;
+  const unsigned koff = (unsigned)(r16 * HD * 2 + grp * 16);  // + c * 64: 16 tokens x 64 bytes
+  const unsigned voff = (unsigned)(grp * HD * 8 + r16 * 16);  // + i * 256: 4 token groups x 256 bytes
+  // this wave's half (K, V) of a page: page pg_w of each step
+  const int pg_w = wave & 3, kv = wave >> 2;
+  const unsigned off = kv ? voff : koff, off_step = kv ? 256u : 64u;
+  auto issue = [&](int phys, int slot) {
+    const uint8_t* b =
+        a.kv_pages + ((((size_t)a.layer * a.n_pages_pool + phys) * 2 + kv) * a.n_heads + head) * blk;
+    const unsigned dst = lds0 + (unsigned)(slot * STAGE + (pg_w * 2 + kv) * NK * 1024);
+#pragma unroll
+    for (int c = 0; c < NK; ++c)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + c * 1024u),
+                   "v"(off + c * off_step), "s"(b)
+                   : "memory");
+  };
+  // this wave's page of the workgroup's k-th step
+  auto page = [&](int k) { return (g + k * stride) * kTreePages + pg_w; };
+  int asked = 0;  // steps requested
+#pragma unroll
+  for (int k = 0; k < kTreeStages; ++k)
+    if (asked == k && page(k) - pg_w + kTreePages <= a.n_arg_pages) {
+      issue(a.pages[page(k)], k);
+      asked = k + 1;
+    }
+
+  const int n_pages = (n_kv + a.item_slots[y] + kPage - 1) / kPage;
+  const int n_st = tree_steps(n_pages);
+  if (head == 0 && g == 0 && threadIdx.x == 0) {  // the split this launch took (inspection)
+    a.split_out[y] = tree_groups(a, n_pages);
+    a.split_out[kAttnMaxItems + y] = Ms;
+    if (y == 0) a.split_out[2 * kAttnMaxItems] = (int)gridDim.y;
+  }
+  if (g >= n_st) {                                 // uniform over the workgroup
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // let the early loads land first
+    return;
+  }
+  const int my_n = (n_st - 1 - g) / stride + 1;    // this workgroup's steps
+  const int32_t* pt = a.page_table + a.pt_off[sq];
+  // ids of the wave's pages of steps k0 .. k0 + 63, one per lane (past the end: the last page)
+  int ids = 0;
+  auto load_ids = [&](int k0) {
+    ids = __builtin_nontemporal_load(pt + min(page(k0 + lane), n_pages - 1));
+  };
+  load_ids(0);
+
+  // row tile and page pair of this wave (with one or two tiles half the waves only load)
+  const int tile = T > 2 ? wave & 3 : wave & 1, pair = T > 2 ? wave >> 2 : wave >> 1;
+  const bool work = tile < T && pair < 2;          // uniform over the wave
+  const int ln = tile * 16 + r16;                  // row of the item
+  const bool in = work && ln < Ms;
+  const uint64_t anc = in ? a.sp->anc[row0 + ln] : 0ull;
+  const int base = n_kv + (in ? (int)a.sp->row_slot0[row0 + ln] : 0);  // slot of its segment's node 0
+  f16x8 q[NK];
+  {
+    const float* qr = a.q + (size_t)(row0 + min(ln, Ms - 1)) * a.d + head * HD + grp * 8;
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+      const float4 x = *(const float4*)(qr + c * 32), z = *(const float4*)(qr + c * 32 + 4);
+      q[c] = f16x8{(_Float16)x.x, (_Float16)x.y, (_Float16)x.z, (_Float16)x.w,
+                   (_Float16)z.x, (_Float16)z.y, (_Float16)z.z, (_Float16)z.w};
+    }
+  }
+  for (; asked < kTreeStages && asked < my_n; ++asked)
+    issue(__builtin_amdgcn_readlane(ids, asked), asked);
+
+  f32x4 O[2 * NK];  // [2 i + j]: dims 32 i + 8 grp + 2 v + j of row r16
+#pragma unroll
+  for (int n = 0; n < 2 * NK; ++n) O[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -1e30f, l_run = 0.f;
+  // Folds two pages from the step's page p0 on into the wave's state.
+  auto fold = [&](const uint8_t* st, int pg0, int p0) {
+    constexpr int NP = 2;
+    f32x4 S[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      S[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NK; ++c)
+        S[p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*(const f16x8*)(st + ((p0 + p) * 2 * NK + c) * 1024), q[c], S[p],
+                                                      0, 0, 0);
+    }
+    // S[p][v]: slot of page p's token 4 grp + v against row r16; past the context a
+    // slot is visible when it holds the row or an ancestor (uniform branch)
+    const int s0 = (pg0 + p0) * kPage + grp * 4;
+    if ((pg0 + p0 + NP) * kPage > n_kv) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int slot = s0 + p * kPage + v;
+          const unsigned j = (unsigned)(slot - base);
+          // without short-circuit: lanes differ (and with it this compiler
+          // hid the visible draft slots too)
+          const bool vis = (slot < n_kv) | ((j < 64u) & (bool)((anc >> (j & 63u)) & 1ull));
+          S[p][v] = vis ? S[p][v] : -INFINITY;
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) mx = fmaxf(mx, S[p][v] * a.scale_log2);
+    mx = fmaxf(m_run, max_col4(mx));
+    const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+    m_run = mx;
+    f16x8 P[NP / 2];
+    float l = 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float e = __builtin_amdgcn_exp2f(S[p][v] * a.scale_log2 - mx);
+        l += e;
+        P[p >> 1][(p & 1) * 4 + v] = (_Float16)e;
+      }
+    l_run = l_run * alpha + l;
+#pragma unroll
+    for (int n = 0; n < 2 * NK; ++n) O[n] *= alpha;
+    // two pages per MFMA: k = 8 grp + 4 b + u is token 4 grp + u of page 2 h + b
+#pragma unroll
+    for (int h = 0; h < NP / 2; ++h)
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        uint4 va = *(const uint4*)(st + ((p0 + 2 * h) * 2 * NK + NK + i) * 1024);
+        uint4 vb = *(const uint4*)(st + ((p0 + 2 * h + 1) * 2 * NK + NK + i) * 1024);
+        if (pg0 + p0 + NP > n_pages) {  // uniform: pages past the item's, whose values are anything
+          if (pg0 + p0 + 2 * h >= n_pages) va = uint4{0, 0, 0, 0};
+          if (pg0 + p0 + 2 * h + 1 >= n_pages) vb = uint4{0, 0, 0, 0};
+        }
+        O[2 * i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, uint4{va.x, va.y, vb.x, vb.y}),
+                                                          P[h], O[2 * i], 0, 0, 0);
+        O[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, uint4{va.z, va.w, vb.z, vb.w}),
+                                                              P[h], O[2 * i + 1], 0, 0, 0);
+      }
+  };
+
+  int slot = 0;
+  for (int k = 0; k < my_n; ++k) {
+    // this wave's page of step k is here once at most the later steps' loads are out
+    const int later = asked - 1 - k;
+    if (later >= 3)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * PW) : "memory");
+    else if (later == 2)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PW) : "memory");
+    else if (later == 1)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PW) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // ... and so is every wave's
+    asm volatile("" ::: "memory");
+    if (work) {
+      const uint8_t* st = tree_ring + slot * STAGE + lane * 16;
+      const int pg0 = (g + k * stride) * kTreePages;
+      fold(st, pg0, 2 * pair);
+    }
+    if (k + kTreeStages < my_n) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();  // step k has been read: its slot may be refilled
+      asm volatile("" ::: "memory");
+      if ((asked & 63) == 0) load_ids(asked);
+      issue(__builtin_amdgcn_readlane(ids, asked & 63), slot);
+      ++asked;
+    }
+    slot = slot + 1 == kTreeStages ? 0 : slot + 1;
+  }
+  // the two waves of a tile meet: every page has been read, and no load (of
+  // steps requested early past the last one) still writes the ring
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  float l = sum_col4(l_run);
+  f32x4* meet = (f32x4*)(tree_ring + tile * ((2 * NK + 1) * 1024)) + lane;
+  if (work && pair == 1) {
+#pragma unroll
+    for (int n = 0; n < 2 * NK; ++n) meet[n * 64] = O[n];
+    meet[2 * NK * 64] = f32x4{m_run, l, 0.f, 0.f};
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (!work || pair == 1) return;
+  {
+    const f32x4 ml = meet[2 * NK * 64];
+    const float m = fmaxf(m_run, ml[0]);
+    const float f0 = __builtin_amdgcn_exp2f(m_run - m), f1 = __builtin_amdgcn_exp2f(ml[0] - m);
+    l = l * f0 + ml[1] * f1;
+    m_run = m;
+#pragma unroll
+    for (int n = 0; n < 2 * NK; ++n) O[n] = O[n] * f0 + meet[n * 64] * f1;
+  }
+
+  const int G = tree_groups(a, n_pages);
+  if (G == 1) {
+    if (!in) return;
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      f16x8 o;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        o[2 * v] = (_Float16)(O[2 * i][v] * inv);
+        o[2 * v + 1] = (_Float16)(O[2 * i + 1][v] * inv);
+      }
+      *(f16x8*)((_Float16*)a.o + act_index<_Float16>(row0 + ln, head * HD + 32 * i + 8 * grp, a.d)) = o;
+    }
+    return;
+  }
+  const size_t part = (((size_t)head * gridDim.y + y) * a.groups + g) * kAttnMaxTiles + tile;
+  float* po = a.part_o + (part * 16 + r16) * HD + 8 * grp;
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    *(float4*)(po + 32 * i) = make_float4(O[2 * i][0], O[2 * i + 1][0], O[2 * i][1], O[2 * i + 1][1]);
+    *(float4*)(po + 32 * i + 4) = make_float4(O[2 * i][2], O[2 * i + 1][2], O[2 * i][3], O[2 * i + 1][3]);
+  }
+  if (grp == 0) *(float2*)(a.part_ml + (part * 16 + r16) * 2) = make_float2(m_run, l);
+}
+
 // The deferred merge: workgroup (head, item, z) combines rows 8 z .. 8 z + 7
 // of the item from its G partial states (plain loads: the attention launch
 // has ended), one thread per four adjacent dimensions of a row, summed in
 // workgroup order; items the attention launch finished itself (G = 1) are
 // skipped.
 constexpr int kMergeRows = 8;
-template <typename TW, int HD, int TMAX>
+template <typename TW, int HD, int TMAX, bool TREE = false>
 __global__ __launch_bounds__(kMergeRows * HD / 4) void k_attn_merge(AttnArgs a) {
   const int head = blockIdx.x, y = blockIdx.y, z = blockIdx.z;
   const int row0 = a.item_row0[y], Ms = a.item_rows[y];
   const int lr = z * kMergeRows + (int)threadIdx.x / (HD / 4);  // row of the item
   if (lr >= Ms) return;
   const int T = (Ms + 15) >> 4;
-  const int G = attn_item_groups(a, (a.sp->seq_nkv[a.item_seg[y]] + a.item_slots[y] + kPage - 1) / kPage, T);
+  const int n_pages = (a.sp->seq_nkv[a.item_seg[y]] + a.item_slots[y] + kPage - 1) / kPage;
+  const int G = TREE ? tree_groups(a, n_pages) : attn_item_groups(a, n_pages, T);
   if (G == 1) return;
   const int dim = ((int)threadIdx.x % (HD / 4)) * 4;
   const int t = lr >> 4, row = lr & 15;
@@ -666,7 +929,7 @@ template <typename TK, typename TW, int HD, int TMAX>
 static hipError_t attn_attr() {
   hipError_t e = hipFuncSetAttribute((const void*)k_attn<TK, TW, HD, TMAX, false>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds<TK, HD, TMAX, false>());
-  if constexpr (sizeof(TK) == 2)
+  if constexpr (sizeof(TK) == 2 && TMAX == 1)
     if (e == hipSuccess)
       e = hipFuncSetAttribute((const void*)k_attn<TK, TW, HD, TMAX, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds<TK, HD, TMAX, true>());
@@ -684,7 +947,12 @@ static hipError_t attn_attr_hd() {
 // Raises the LDS limit of the attention kernels (more than 64 KiB); done once
 // at context creation so that no attribute call falls inside a captured step.
 hipError_t init_kernel_attributes() {
-  hipError_t e = attn_attr_hd<_Float16, _Float16, 128>();
+  hipError_t e = hipFuncSetAttribute((const void*)k_attn_tree<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)tree_lds<128>());
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)k_attn_tree<64>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)tree_lds<64>());
+  if (e == hipSuccess) e = attn_attr_hd<_Float16, _Float16, 128>();
   if (e == hipSuccess) e = attn_attr_hd<_Float16, _Float16, 64>();
   if (e == hipSuccess) e = attn_attr_hd<float, float, 128>();
   if (e == hipSuccess) e = attn_attr_hd<float, float, 64>();
@@ -695,7 +963,7 @@ template <typename TK, typename TW, int HD, int TMAX>
 static hipError_t attn_t(int n_seq, const AttnArgs& a, hipStream_t s) {
   constexpr size_t lds_one = attn_lds<TK, HD, TMAX, false>();
   bool launched = false;
-  if constexpr (sizeof(TK) == 2) {
+  if constexpr (sizeof(TK) == 2 && TMAX == 1) {
     if (a.pages_per_wg == 0) {  // one KV sequence: the paired walk
       constexpr size_t lds_pair = attn_lds<TK, HD, TMAX, true>();
       TSS_LAUNCH((k_attn<TK, TW, HD, TMAX, true>), dim3(a.n_heads, n_seq, a.groups), dim3(kAttnWaves * 64),
@@ -715,6 +983,16 @@ static hipError_t attn_t(int n_seq, const AttnArgs& a, hipStream_t s) {
   return e;
 }
 
+template <int HD>
+static hipError_t attn_tree(int n_items, const AttnArgs& a, hipStream_t s) {
+  TSS_LAUNCH(k_attn_tree<HD>, dim3(a.n_heads, n_items, a.groups), dim3(kTreeWaves * 64), tree_lds<HD>(), s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  TSS_LAUNCH((k_attn_merge<_Float16, HD, kAttnMaxTiles, true>),
+             dim3(a.n_heads, n_items, kAttnMaxTiles * 16 / kMergeRows), dim3(kMergeRows * HD / 4), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename TK, typename TW, int HD>
 static hipError_t attn_hd(int tiles, int n_seq, const AttnArgs& a, hipStream_t s) {
   if (tiles <= 1) return attn_t<TK, TW, HD, 1>(n_seq, a, s);
@@ -725,6 +1003,8 @@ static hipError_t attn_hd(int tiles, int n_seq, const AttnArgs& a, hipStream_t s
 // max_tiles = most 16-row tiles of an item (1..4); n_seq = items (grid.y).
 hipError_t launch_attn(bool bf16, int head_dim, int max_tiles, int n_seq, const AttnArgs& a, hipStream_t s) {
   if (max_tiles < 1 || max_tiles > 4 || n_seq < 1 || n_seq > kAttnMaxItems) return hipErrorInvalidValue;
+  if (bf16 && max_tiles >= 2 && a.pages_per_wg == 0)
+    return head_dim == 128 ? attn_tree<128>(n_seq, a, s) : attn_tree<64>(n_seq, a, s);
   if (bf16)
     return head_dim == 128 ? attn_hd<_Float16, _Float16, 128>(max_tiles, n_seq, a, s)
                            : attn_hd<_Float16, _Float16, 64>(max_tiles, n_seq, a, s);

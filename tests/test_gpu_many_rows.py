@@ -79,3 +79,55 @@ def test_one_tree_of_many_rows(model, n):
     e = _rel(v.logits(n), verify(m, oseqs[3], tok, par).logits)
     log(f"{shape.name} tree of {n}: rel {e:.2e}")
     assert e <= REL
+
+
+@pytest.mark.parametrize("ctx_len", [0, 1, 15, 16, 31, 48, 63, 64, 65, 130])
+def test_tree_attention_at_page_and_step_edges(model, ctx_len):
+    """Trees of 2 to 4 row tiles behind contexts that end at, before and after a page and a four-page step."""
+    shape, v, m, _ = model
+    s, L = 7, shape.n_layers
+    ctx = synth.context_tokens(shape.vocab, ctx_len, stream=700 + ctx_len)
+    v.truncate(s, 0)
+    v.set_mask(s, None)
+    if ctx_len:
+        v.prefill(s, ctx)
+    o = OracleSequence(m)
+    if ctx_len:
+        prefill(m, o, ctx)
+    for n in (17, 33, 50, 64):
+        tok = synth.context_tokens(shape.vocab, n, stream=800 + n)
+        par = synth.random_tree(n, stream=800 + n, max_children=3)
+        v.verify(s, tok, par)
+        e = _rel(v.logits(n), verify(m, o, tok, par).logits)
+        log(f"{shape.name} context {ctx_len} tree {n}: rel {e:.2e}, split {v.attn_split()}")
+        assert e <= REL
+
+
+def test_tree_attention_of_many_steps_per_workgroup():
+    """128 heads and two items leave one workgroup per head and item, which walks 66 steps (two reads of its
+    page ids) past the page ids in the arguments.  Each checked node's row against its root path verified as
+    a chain of at most 16 nodes (another kernel), under both masks."""
+    shape = synth.ModelShape("rows-h128", 96, n_layers=2, d_model=8192, n_heads=128, head_dim=64, ffn_dim=64, vocab=416,
+                             dtype="bf16")
+    pages = (4360 + 15) // 16
+    v = gpu_verifier(shape, n_seqs=1, max_tokens=4360, max_nodes=64, max_batch=2,
+                     page_order=np.random.default_rng(9).permutation(pages))
+    ctx = synth.context_tokens(shape.vocab, 4200, stream=900)
+    v.prefill(0, ctx)
+    tok = synth.context_tokens(shape.vocab, 64, stream=901)
+    par = synth.random_tree(64, stream=902, max_children=4)
+    masks = np.array([[0, 0], [0, 1]], dtype=np.uint8)
+    v.verify_sweep(0, tok, masks, par, reuse_prefix=False)
+    got = v.logits(128).reshape(2, 64, -1)
+    for node in (0, 1, 30, 47, 63):
+        path = [node]
+        while par[path[-1]] >= 0:
+            path.append(int(par[path[-1]]))
+        path = path[::-1]
+        assert len(path) <= 16
+        for k in (0, 1):
+            v.verify(0, tok[path], None, masks[k])
+            e = _rel(got[k, node], v.logits(len(path))[-1])
+            log(f"node {node} depth {len(path) - 1} mask {k}: rel {e:.2e}")
+            assert e <= REL
+    v.close()
