@@ -120,7 +120,9 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
 // the store has landed) runs one accept scan per sequence over its tree: a
 // node is accepted when its parent is and its token equals the parent's
 // greedy token; the deepest accepted node (lowest id among equal depths)
-// gives accept_len and the bonus token.
+// gives accept_len and the bonus token.  One wave takes a sequence, one lane a
+// node (one thread walking the nodes took most of a 61-node launch: 10.8 ->
+// 6.5 us).
 constexpr int kAcceptThreads = 256;
 constexpr int kAcceptLoads = 8;  // partials per thread per round (2048 per round: V = 32000 in one)
 __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
@@ -131,8 +133,21 @@ __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
   __shared__ int32_t s_tok[kMaxRows];
   __shared__ int8_t s_par[kMaxRows];
   __shared__ uint8_t s_dep[kMaxRows];
+  __shared__ uint64_t s_anc[kMaxRows];
+  __shared__ int s_row0[kMaxSegs + 1];
   const int m = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int M = a.M;
+  // what the scan needs beside the greedy tokens, by every workgroup (any may
+  // be the last): on its way while the partials are reduced
+  for (int i = threadIdx.x; i < M; i += kAcceptThreads) {
+    s_tok[i] = a.sp->tok[i];
+    s_par[i] = a.sp->parent[i];
+    s_dep[i] = a.sp->depth[i];
+    s_anc[i] = a.sp->anc[i];
+  }
+  const int n_seqs = a.sp->n_seqs;
+  if (threadIdx.x <= n_seqs) s_row0[threadIdx.x] = a.sp->seq_row0[threadIdx.x];
   // the row's partials through buffer resources: loads past the row return
   // zeros (replaced below), so none needs a branch
   const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
@@ -186,38 +201,33 @@ __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
   __syncthreads();
   if (!last) return;
 
-  const int M = a.M;
-  for (int i = threadIdx.x; i < M; i += kAcceptThreads) {
+  for (int i = threadIdx.x; i < M; i += kAcceptThreads)
     g[i] = __hip_atomic_load(a.greedy + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_tok[i] = a.sp->tok[i];
-    s_par[i] = a.sp->parent[i];
-    s_dep[i] = a.sp->depth[i];
-  }
   __syncthreads();
-  const int sq = threadIdx.x;
-  if (sq < a.sp->n_seqs) {
-    const int r0 = a.sp->seq_row0[sq], n = a.sp->seq_row0[sq + 1] - r0;
+  // one wave per segment, one lane per node: a node is accepted when it and
+  // every ancestor match the greedy token of their parents
+  for (int sq = wave; sq < n_seqs; sq += kAcceptThreads / 64) {
+    const int r0 = s_row0[sq], n = s_row0[sq + 1] - r0;
     const int32_t* gs = g + r0;
-    uint64_t acc = 1ull;  // bit i: local node i accepted
-    int best = 0;
-    for (int i = 1; i < n; ++i) {
-      const int p = s_par[r0 + i];
-      if (((acc >> p) & 1ull) && s_tok[r0 + i] == gs[p]) {
-        acc |= 1ull << i;
-        if (s_dep[r0 + i] > s_dep[r0 + best]) best = i;
-      }
-    }
-    const int len = s_dep[r0 + best];
+    const bool node = lane < n;
+    const int r = r0 + (node ? lane : 0);
+    const uint64_t matched = __ballot(node && (lane == 0 || s_tok[r] == gs[max((int)s_par[r], 0)]));
+    // deepest accepted node, lowest id among equal depths (the root always is)
+    int key = node && (s_anc[r] & ~matched) == 0 ? (s_dep[r] << 8) | (255 - lane) : 255;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
+    const int best = 255 - (key & 255), len = key >> 8;
+    const bool on_path = (s_anc[r0 + best] >> lane) & 1ull;
+#pragma unroll
     for (int copy = 0; copy < 2; ++copy) {
-      Result* r = (copy == 0 ? a.result : a.result_host) + sq;
-      r->accept_len = len;
-      r->next_token = gs[best];
-      r->best = best;
-      r->path_len = len + 1;
-      for (int j = best, dd = len; dd >= 0; --dd) {
-        r->path[dd] = j;
-        j = dd > 0 ? s_par[r0 + j] : 0;
+      Result* res = (copy == 0 ? a.result : a.result_host) + sq;
+      if (lane == 0) {
+        res->accept_len = len;
+        res->next_token = gs[best];
+        res->best = best;
+        res->path_len = len + 1;
       }
+      if (on_path) res->path[s_dep[r]] = lane;
     }
   }
   if (threadIdx.x == 0) *a.count = 0;
