@@ -111,9 +111,12 @@ constexpr int kAttnWaves = TSS_ATTN_WAVES;
 // Workgroups an item's n_pages pages are divided among: at most `groups`, at
 // least a page per wave, few enough that the partial states (T tiles each)
 // stay well below the pages, and in a batch of sequences one per
-// pages_per_wg pages.  The attention and merge launches derive it alike.
+// pages_per_wg pages; one up to two pages per wave, where meeting the other
+// workgroups costs more than the second page (tiny decoder at 134 tokens: 7.9
+// -> 6.6 us a launch).  The attention and merge launches derive it alike.
 __device__ __forceinline__ int attn_item_groups(const AttnArgs& a, int n_pages, int T) {
   const int cap = a.pages_per_wg > 0 ? min(a.groups, (n_pages + a.pages_per_wg - 1) / a.pages_per_wg) : a.groups;
+  if (n_pages <= 2 * kAttnWaves) return 1;
   return max(1, min(cap, min((n_pages + kAttnWaves - 1) / kAttnWaves, n_pages / (TSS_ATTN_PART_DIV * T))));
 }
 
@@ -217,12 +220,12 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(AttnArgs a) {
   const bool early = p < arg_pages;
   if (early) load_phys(a.pages[p], kcur, vcur);
 
-  const int sq = a.item_seg[y];
+  const int sq = a.item[y].seg;
   const int n_kv = a.sp->seq_nkv[sq];
-  const int row0 = a.item_row0[y];
-  const int Ms = a.item_rows[y];                     // rows of the item
+  const int row0 = a.item[y].row0;
+  const int Ms = a.item[y].rows;                     // rows of the item
   const int T = (Ms + 15) >> 4;                      // its row tiles (<= TMAX)
-  const int n_pages = (n_kv + a.item_slots[y] + kPage - 1) / kPage;
+  const int n_pages = (n_kv + a.item[y].slots + kPage - 1) / kPage;
   const int G = attn_item_groups(a, n_pages, T);
   if (head == 0 && g == 0 && threadIdx.x == 0) {  // the split this launch took (inspection)
     a.split_out[y] = G;
@@ -650,10 +653,10 @@ __global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
   const int head = blockIdx.x, y = blockIdx.y, g = blockIdx.z;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r16 = lane & 15, grp = lane >> 4;
-  const int row0 = a.item_row0[y], Ms = a.item_rows[y], T = (Ms + 15) >> 4;
+  const int row0 = a.item[y].row0, Ms = a.item[y].rows, T = (Ms + 15) >> 4;
   const int stride = a.groups;             // steps between a workgroup's steps
   // read ahead of the page loads, as a scalar: a vector load's wait would cover them
-  const int sq = a.item_seg[y];
+  const int sq = a.item[y].seg;
   const int n_kv = a.sp->seq_nkv[sq];
 
   const size_t blk = 16 * (size_t)HD * 2;  // bytes of a page's K block of one head
@@ -683,7 +686,7 @@ __global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
       asked = k + 1;
     }
 
-  const int n_pages = (n_kv + a.item_slots[y] + kPage - 1) / kPage;
+  const int n_pages = (n_kv + a.item[y].slots + kPage - 1) / kPage;
   const int n_st = tree_steps(n_pages);
   if (head == 0 && g == 0 && threadIdx.x == 0) {  // the split this launch took (inspection)
     a.split_out[y] = tree_groups(a, n_pages);
@@ -884,11 +887,11 @@ constexpr int kMergeRows = 8;
 template <typename TW, int HD, int TMAX, bool TREE = false>
 __global__ __launch_bounds__(kMergeRows * HD / 4) void k_attn_merge(AttnArgs a) {
   const int head = blockIdx.x, y = blockIdx.y, z = blockIdx.z;
-  const int row0 = a.item_row0[y], Ms = a.item_rows[y];
+  const int row0 = a.item[y].row0, Ms = a.item[y].rows;
   const int lr = z * kMergeRows + (int)threadIdx.x / (HD / 4);  // row of the item
   if (lr >= Ms) return;
   const int T = (Ms + 15) >> 4;
-  const int n_pages = (a.sp->seq_nkv[a.item_seg[y]] + a.item_slots[y] + kPage - 1) / kPage;
+  const int n_pages = (a.sp->seq_nkv[a.item[y].seg] + a.item[y].slots + kPage - 1) / kPage;
   const int G = TREE ? tree_groups(a, n_pages) : attn_item_groups(a, n_pages, T);
   if (G == 1) return;
   const int dim = ((int)threadIdx.x % (HD / 4)) * 4;

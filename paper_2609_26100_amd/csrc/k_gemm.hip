@@ -162,7 +162,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   constexpr int COLS = NT * 16;
   extern __shared__ float smem[];
 
-  const int waves = blockDim.x >> 6;
+  const int waves = a.waves, threads = waves * 64;  // (the block's size would be another line of the arguments)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r16 = lane & 15, grp = lane >> 4;
   const int M = a.M, K = a.K, nkc = a.nkc;
@@ -207,7 +207,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   __shared__ int2 s_col[EPI == EPI_QKV ? COLS : 1];  // per column: section | head << 2, dim | rotary index << 16
   __shared__ const float* s_gain[EPI == EPI_RESID ? kMaxRows : 1];    // next-norm gain of the row's segment
   if constexpr (EPI == EPI_QKV || EPI == EPI_RESID) {
-    for (int r = threadIdx.x; r < M; r += blockDim.x) {
+    for (int r = threadIdx.x; r < M; r += threads) {
       const int sq = a.n_seqs == 1 ? 0 : a.sp->row_seq[r];
       s_seq[r] = sq;
       if constexpr (EPI == EPI_QKV) {
@@ -248,13 +248,13 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   // offset past the buffer's end, which the hardware answers with zeros
   // without touching memory (no branch, so the load-count waits stay exact).
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)x, (short)0, (int)((size_t)S * (a.x_plane > 0 ? a.x_plane : (size_t)a.Mp * K) * sizeof(T)), 0x00020000);
+      (void*)x, (short)0, (int)((size_t)a.Mp * K * sizeof(T)), 0x00020000);
+  static_assert(S == 1, "one activation plane");
   constexpr int kPastEnd = 1 << 30;
   int xoff[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
     xoff[mt] = mt * 16 + r16 < M ? (mt * nkc * 64 + lane) * 16 : kPastEnd;
-  const int plane_bytes = (int)(a.x_plane * sizeof(T));
   auto issue = [&](uint4 (&w)[NT], uint4 (&xs)[MT][S], int i) {
     const int c = c_lo + wave + i * waves;
 #pragma unroll
@@ -264,7 +264,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
 #pragma unroll
       for (int p = 0; p < S; ++p) {
         typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(xres, xoff[mt] + c * kTileBytes + p * plane_bytes, 0, 0);
+        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(xres, xoff[mt] + c * kTileBytes, 0, 0);
         xs[mt][p] = uint4{v.x, v.y, v.z, v.w};
       }
   };
@@ -283,6 +283,11 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   if (n_my > 0) {
 #pragma unroll
     for (int j = 0; j < D; ++j) issue(wv[j], xv[j], min(j, n_my - 1));
+    // the epilogue's arguments, first touched here, where the weights' latency hides it
+    if constexpr (EPI == EPI_QKV) asm volatile("" ::"s"(a.q), "s"(a.n_arg_pages), "s"(a.pages[0]));
+    if constexpr (EPI == EPI_RESID) asm volatile("" ::"s"(a.h), "s"(a.g_next[0]), "s"(a.row_on[0]));
+    if constexpr (EPI == EPI_SWIGLU) asm volatile("" ::"s"(a.act), "s"(a.eps));
+    if constexpr (EPI == EPI_LOGITS) asm volatile("" ::"s"(a.logits), "s"(a.eps));
     int i0 = 0;
     for (; i0 + 2 * D <= n_my; i0 += D) {
 #pragma unroll
@@ -311,14 +316,14 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   // publish them.
   const RowBits rows(a);
   if constexpr (EPI == EPI_QKV) {
-    for (int r = threadIdx.x; r < M; r += blockDim.x) {
+    for (int r = threadIdx.x; r < M; r += threads) {
       const int lp = s_slot[r] >> 4;
       if (rows.on(r)) s_page[r] = lp < a.n_arg_pages ? a.pages[lp] : a.page_table[a.pt_off[s_seq[r]] + lp];
     }
     // the strip's columns: section (q, k, v), head, the head dimension the
     // packing put there and its rotary index (divisions once per column)
     const int d16 = a.d >> 4, hd16 = a.head_dim >> 4;
-    for (int col = threadIdx.x; col < COLS; col += blockDim.x) {
+    for (int col = threadIdx.x; col < COLS; col += threads) {
       const int n = strip * COLS + col;
       const int tile = n >> 4, c = n & 15;
       const int sec = tile / d16, ts = tile % d16;
@@ -329,7 +334,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
   }
   if constexpr (EPI == EPI_RESID) {
     if (a.n_seqs > 1)
-      for (int r = threadIdx.x; r < M; r += blockDim.x) s_gain[r] = a.g_next[s_seq[r]];
+      for (int r = threadIdx.x; r < M; r += threads) s_gain[r] = a.g_next[s_seq[r]];
   }
 
   // LDS: red[waves][ROWS][RCP] | yfin[ROWS][COLS] | aux[ROWS][COLS] | rscale[ROWS]
@@ -422,7 +427,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
           red[(wave * ROWS + mt * 16 + grp * 4 + v) * RCP + nt * 16 - c0 + r16] = acc[mt][nt][v];
     if (c0 == 0 && ss_vec) {
       ss_finish(0);
-      for (int r0 = (int)blockDim.x / 8; r0 < M; r0 += (int)blockDim.x / 8) {
+      for (int r0 = threads / 8; r0 < M; r0 += threads / 8) {
         ss_load(r0);
         ss_finish(r0);
       }
@@ -434,7 +439,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
       // plane (the same operations as summing into yfin first)
       constexpr int PP = RC / 32;  // gate/up pairs per pass
       const int F = a.N >> 1;
-      for (int it = threadIdx.x; it < M * PP * 4; it += blockDim.x) {
+      for (int it = threadIdx.x; it < M * PP * 4; it += threads) {
         const int row = it / (PP * 4), jp = (it >> 2) % PP, c = (it & 3) * 4;
         const float* rg = red + row * RCP + jp * 32 + c;
         float4 g = make_float4(0.f, 0.f, 0.f, 0.f), u = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -453,7 +458,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
                       make_float4(silu(g.x) * u.x, silu(g.y) * u.y, silu(g.z) * u.z, silu(g.w) * u.w));
       }
     } else {
-      for (int e = threadIdx.x; e < M * RC; e += blockDim.x) {
+      for (int e = threadIdx.x; e < M * RC; e += threads) {
         const int row = e / RC, col = e % RC;
         float s = 0.f;
         for (int w = 0; w < waves; ++w) s += red[(w * ROWS + row) * RCP + col];
@@ -474,7 +479,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc(
         a.kpart, (short)0, (int)(gridDim.x * slot_floats * sizeof(float)), 0x00020000);
     constexpr int kScopeAgent = 16;  // cache-policy operand: sc1 (agent scope)
-    for (int e4 = threadIdx.x; e4 < M * COLS / 4; e4 += blockDim.x)
+    for (int e4 = threadIdx.x; e4 < M * COLS / 4; e4 += threads)
       __builtin_amdgcn_raw_buffer_store_b128(*(const f4v*)(yfin + 4 * e4), pres,
                                              (int)((blockIdx.x * slot_floats + 4 * e4) * sizeof(float)), 0,
                                              kScopeAgent);
@@ -489,12 +494,12 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     // thread at a time, with all their requests (the other splits' partial
     // tiles, h, the next norm's gain) issued together.
     const int N = a.N, n4 = M * COLS / 4;
-    for (int b0 = threadIdx.x; b0 < n4; b0 += 2 * (int)blockDim.x) {
+    for (int b0 = threadIdx.x; b0 < n4; b0 += 2 * threads) {
       f4v v[2][kMaxKSplit];
       float4 h0[2], gn[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int e4 = min(b0 + u * (int)blockDim.x, n4 - 1);  // clamped: every thread loads
+        const int e4 = min(b0 + u * threads, n4 - 1);  // clamped: every thread loads
         const int row = e4 / (COLS / 4), col = (e4 % (COLS / 4)) * 4;
 #pragma unroll
         for (int k = 0; k < kMaxKSplit; ++k)
@@ -506,7 +511,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int e4 = b0 + u * (int)blockDim.x;
+        const int e4 = b0 + u * threads;
         if (e4 >= n4) break;
         const int row = e4 / (COLS / 4), col = (e4 % (COLS / 4)) * 4;
         const f4v own = *(const f4v*)(yfin + 4 * e4);
@@ -554,7 +559,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
       }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < M * COLS; e += blockDim.x) yfin[e] *= rscale[e / COLS];
+    for (int e = threadIdx.x; e < M * COLS; e += threads) yfin[e] *= rscale[e / COLS];
   }
   if constexpr (!FUSED) __syncthreads();
 
@@ -565,12 +570,12 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     // with 8 waves, at most 8): the batch's rotary coefficients are requested
     // together before any of its stores, so they cost one round trip.
     constexpr int QB = (ROWS * COLS + 511) / 512 > 8 ? 8 : (ROWS * COLS + 511) / 512;
-    for (int e0 = threadIdx.x; e0 < M * COLS; e0 += QB * (int)blockDim.x) {
+    for (int e0 = threadIdx.x; e0 < M * COLS; e0 += QB * threads) {
       float2 cs[QB];
       int sec[QB], head[QB], dim[QB];
 #pragma unroll
       for (int j = 0; j < QB; ++j) {
-        const int e = e0 + j * (int)blockDim.x;
+        const int e = e0 + j * threads;
         if (e < M * COLS) {
           const int row = e / COLS;
           const int2 ci = s_col[e % COLS];
@@ -584,7 +589,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
       }
 #pragma unroll
       for (int j = 0; j < QB; ++j) {
-        const int e = e0 + j * (int)blockDim.x;
+        const int e = e0 + j * threads;
         if (e >= M * COLS) break;
         const int row = e / COLS, col = e % COLS, c = col & 15;
         float val = yfin[row * COLS + col];
@@ -612,12 +617,12 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     // four adjacent columns per thread: vector loads and stores of h, the
     // gain and the next-norm input (adjacent in each activation plane)
     const int N = a.N;
-    for (int e4 = threadIdx.x; e4 < (split_done ? 0 : M * COLS / 4); e4 += blockDim.x) {
+    for (int e4 = threadIdx.x; e4 < (split_done ? 0 : M * COLS / 4); e4 += threads) {
       const int row = e4 / (COLS / 4), col = (e4 % (COLS / 4)) * 4;
       if (!rows.on(row)) continue;
       const size_t idx = (size_t)row * N + n0 + col;
       // one pass (always with one row tile): the operands prefetched for e4
-      const bool pre = PRE_RESID && M * COLS / 4 <= (int)blockDim.x && n_my > 0;
+      const bool pre = PRE_RESID && M * COLS / 4 <= threads && n_my > 0;
       float4 h0, gn;
       if (pre)
         h0 = pre_h;
@@ -636,7 +641,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     }
     __syncthreads();
     // one partial sum of h^2 per 16 columns (the format every norm reads)
-    for (int e = threadIdx.x; e < M * NT; e += blockDim.x) {
+    for (int e = threadIdx.x; e < M * NT; e += threads) {
       const int row = e / NT, j = e % NT;
       if (!rows.on(row)) continue;
       float s = 0.f;
@@ -648,7 +653,7 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     const int F = a.N >> 1;
     constexpr int PAIRS = NT / 2;
     // four adjacent outputs per thread, one vector store per plane
-    for (int e4 = threadIdx.x; e4 < M * 4 * PAIRS; e4 += blockDim.x) {
+    for (int e4 = threadIdx.x; e4 < M * 4 * PAIRS; e4 += threads) {
       const int row = e4 / (4 * PAIRS), j = (e4 / 4) % PAIRS, c = (e4 & 3) * 4;
       const float* g = yfin + row * COLS + j * 32 + c;
       const float* u = g + 16;
@@ -657,13 +662,13 @@ __device__ __forceinline__ void gemm_body(GemmArgs a, int pair0 = 0) {
     }
   } else if constexpr (EPI == EPI_LOGITS) {
     const int N = a.N;
-    for (int e = threadIdx.x; e < M * COLS; e += blockDim.x) {
+    for (int e = threadIdx.x; e < M * COLS; e += threads) {
       const int row = e / COLS, col = e % COLS;
       a.logits[(size_t)row * N + n0 + col] = yfin[row * COLS + col];
     }
     // one (max, argmax) per 16 columns, lowest column on ties; NaN counts as
     // the largest value (first NaN wins), as in numpy's argmax
-    for (int e = threadIdx.x; e < M * NT; e += blockDim.x) {
+    for (int e = threadIdx.x; e < M * NT; e += threads) {
       const int row = e / NT, j = e % NT;
       float bv = yfin[row * COLS + j * 16];
       int bi = j * 16;
@@ -762,7 +767,7 @@ hipError_t init_gemm_attributes() {
 }
 
 template <typename T, int MT, int NT, int EPI>
-static hipError_t launch_v(const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_v(GemmArgs a, hipStream_t s) {
   // 8 waves (measured best across the 7B shapes) unless K is short, capped by
   // LDS: up to 64 rows the cross-wave reduction stays within 64 KiB
   // (4-tile blocks and more than 4 row tiles may use most of the CU's LDS)
@@ -771,13 +776,14 @@ static hipError_t launch_v(const GemmArgs& a, hipStream_t s) {
   int waves = nkc_min < 8 ? nkc_min : 8;
   while (waves > 1 && gemm_lds<MT, NT, EPI>(waves) > cap) waves >>= 1;
   const size_t lds = gemm_lds<MT, NT, EPI>(waves);
+  a.waves = waves;
   dim3 grid(a.N / (16 * NT) * a.ksplit), block(waves * 64);
   TSS_LAUNCH((k_gemm<T, MT, NT, EPI>), grid, block, lds, s, a);
   return hipGetLastError();
 }
 
 template <typename T, int MT, int NT>
-static hipError_t launch_gu2(const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_gu2(GemmArgs a, hipStream_t s) {
   const int nkc_min = a.nkc;
   int waves = nkc_min < 8 ? nkc_min : 8;
   auto lds_of = [](int w) {
@@ -785,6 +791,7 @@ static hipError_t launch_gu2(const GemmArgs& a, hipStream_t s) {
     return lw > ln ? lw : ln;
   };
   while (waves > 1 && lds_of(waves) > gemm_lds_cap<MT, NT>()) waves >>= 1;
+  a.waves = waves;
   TSS_LAUNCH((k_gemm_gu2<T, MT, NT>), dim3(kGemmRound), dim3(waves * 64), lds_of(waves), s, a);
   return hipGetLastError();
 }

@@ -922,10 +922,10 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
         if (n_act == kAttnMaxItems) return fail(c, TSS_EINVAL, "too many attention items in one step");
         const int rows = std::min(64, hi - r);
         const int last_seg = sp.row_seq[r + rows - 1];
-        at.item_row0[n_act] = r;
-        at.item_rows[n_act] = rows;
-        at.item_seg[n_act] = sp.row_seq[r];
-        at.item_slots[n_act] = sp.seg_slot0[last_seg] + sp.seq_row0[last_seg + 1] - sp.seq_row0[last_seg];
+        at.item[n_act].row0 = r;
+        at.item[n_act].rows = rows;
+        at.item[n_act].seg = sp.row_seq[r];
+        at.item[n_act].slots = sp.seg_slot0[last_seg] + sp.seq_row0[last_seg + 1] - sp.seq_row0[last_seg];
         max_tiles = std::max(max_tiles, (rows + 15) / 16);
         ++n_act;
       }
@@ -940,7 +940,6 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       GemmArgs a = lb;
       a.w = c->w + W.qkv;
       a.x = ws + c->wsl.xa;
-      a.x_plane = plane_d;
       a.K = d;
       a.N = 3 * d;
       a.nkc = d / c->KC;
@@ -997,7 +996,6 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       GemmArgs a = lb;
       a.w = c->w + W.o;
       a.x = ws + c->wsl.o;
-      a.x_plane = plane_d;
       a.K = d;
       a.N = d;
       a.nkc = d / c->KC;
@@ -1016,7 +1014,6 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       GemmArgs a = lb;
       a.w = c->w + W.gateup;
       a.x = ws + c->wsl.xm;
-      a.x_plane = plane_d;
       a.K = d;
       a.N = 2 * f;
       a.nkc = d / c->KC;
@@ -1031,7 +1028,6 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       GemmArgs a = lb;
       a.w = c->w + W.down;
       a.x = ws + c->wsl.act;
-      a.x_plane = plane_f;
       a.K = f;
       a.N = d;
       a.nkc = f / c->KC;
@@ -1053,7 +1049,6 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
       GemmArgs a = base;
       a.w = c->w + c->wl.lm_head;
       a.x = ws + c->wsl.xa;
-      a.x_plane = plane_d;
       a.K = d;
       a.N = cf.vocab;
       a.nkc = d / c->KC;

@@ -177,20 +177,30 @@ struct Result {
 
 enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 
-struct GemmArgs {
+// Kernel arguments are read a 64-byte line at a time, each first touch a round
+// trip to the argument block, so the fields stand in the order of their use:
+// what the prologue needs in the first two lines, what the epilogues need in
+// the next two, the long arrays behind (7B one-node step 415 -> 408 us, k = 5
+// step 428 -> 424, with the kernels' own first touches of the epilogue lines
+// behind the weight ring's first loads).
+struct alignas(64) GemmArgs {
   const uint8_t* w;        // packed weights of this matrix
-  const void* x;           // A operand [Mp][K] of T in tile order (act_index), planes x_plane elements apart
-  size_t x_plane;
-  int M, K, N;             // N = packed output columns
-  int nkc;                 // K / KC
+  const void* x;           // A operand [Mp][K] of T in tile order (act_index)
   // RMSNorm of the A rows: x holds T(h * gain); the row scale
   // rsqrt(sum(h^2) / norm_dim + eps) is applied to the products here.
   const float* ss_in;      // [M][ss_stride] partial sums of h^2, ss_nparts used (null: no norm)
+  const StepParams* sp;
+  int M, K, N;             // N = packed output columns
+  int nkc;                 // K / KC
   int ss_nparts;
   int ss_stride;           // row stride of ss_in / ss_out (parts)
-  int norm_dim;
-  float eps;
-  int Mp;                  // row stride of the partial-sum arrays
+  int Mp;                  // rows of the operand and output buffers
+  int waves;               // waves per workgroup (k_gemm; set by its launcher)
+
+  // rows whose segment runs this block (bit r of row_on[r / 64]); the QKV
+  // and residual epilogues write nothing for the other rows
+  uint64_t row_on[kMaxRows / 64];
+  int n_seqs;              // segments
   // K split (> 1): workgroup blockIdx.x takes strip blockIdx.x / ksplit over
   // its share of K; the ksplit partial products of a strip meet in kpart
   // (agent-scope accesses) and the last workgroup to arrive finishes the strip
@@ -198,44 +208,43 @@ struct GemmArgs {
   // gate/up in blocks of two widths (gemm_wide_wgs > 0): workgroups
   // [0, wide_wgs) take NT / 2 pairs, the rest NT / 2 - 1
   int wide_wgs;
-  float* kpart;            // [strips * ksplit][Mp][16 * NT] partial products
-  int* kcount;             // [strips] arrivals, zero between launches
-  const StepParams* sp;
+  int norm_dim;
+  float eps;
+  int pre_n0;              // prompt rows (k_tile): position and KV slot of row 0
   const StepRows* rows;    // k_tile's Q/K/V of a step
-  // rows whose segment runs this block (bit r of row_on[r / 64]); the QKV
-  // and residual epilogues write nothing for the other rows
-  uint64_t row_on[kMaxRows / 64];
-  int n_seqs;              // segments
+  const int32_t* page_table;  // the pool's page table; segment s's sequence's pages start at pt_off[s]
+  int am_stride;
+  int32_t n_arg_pages;     // with one KV sequence in the step: valid entries of pages[] (else 0)
+
   // EPI_QKV
   float* q;                // [Mp][d]
   uint8_t* kv_pages;       // first page of the pool
-  const int32_t* page_table;  // the pool's page table; segment s's sequence's pages start at pt_off[s]
-  int32_t pt_off[kMaxSegs];
-  int32_t n_arg_pages;     // with one KV sequence in the step: valid entries of pages[] (else 0)
-  int32_t pages[kArgPages];  // physical ids of that sequence's first pages
   const float2* rope;      // [max_pos][hd/2] (cos, sin)
   int layer, n_pages_pool, n_heads, head_dim, d;
-  int pre_n0;              // prompt rows (k_tile): position and KV slot of row 0
+  // EPI_SWIGLU
+  void* act;               // [Mp][N/2] activation plane of silu(gate) * up
+  size_t act_plane;
+
   // EPI_RESID
   float* h;                // [Mp][N] residual, updated in place
-  void* xn;                // [Mp][N] activation planes of h_new * g_next
+  void* xn;                // [Mp][N] activation plane of h_new * g_next
   size_t xn_plane;
-  const float* g_next[kMaxSegs];   // gain of each segment's next RMSNorm
   float* ss_out;           // [M][ss_stride] partial sums of h_new^2, one per strip
-  // EPI_SWIGLU
-  void* act;               // [Mp][N/2] activation planes of silu(gate) * up
-  size_t act_plane;
+  float* kpart;            // [strips * ksplit][Mp][16 * NT] partial products
+  int* kcount;             // [strips] arrivals, zero between launches
+  const float* g_next[kMaxSegs];   // gain of each segment's next RMSNorm
   // EPI_LOGITS
   float* logits;           // [Mp][N]
   float* am_val;           // [M][am_stride] per-strip (max, argmax)
   int32_t* am_idx;
-  int am_stride;
+  int32_t pt_off[kMaxSegs];
+  int32_t pages[kArgPages];  // physical ids of that sequence's first pages
 };
 
 // An attention item is a range of at most 64 consecutive rows of one KV
 // sequence (grid.y walks the items): its workgroups read the sequence's pages
 // once for all of its rows, whatever segments they belong to.
-struct AttnArgs {
+struct alignas(64) AttnArgs {
   const float* q;          // [Mp][d] row-major
   const uint8_t* kv_pages;
   const int32_t* page_table;
@@ -254,37 +263,41 @@ struct AttnArgs {
   int defer_merge;         // partial states merged by a second launch (launches with items of 2+ row tiles)
   int layer, n_pages_pool, n_heads, d;
   float scale_log2;        // log2(e) / sqrt(hd)
-  // per item, 32-bit so that the kernel reads them with scalar loads
-  int32_t item_row0[kAttnMaxItems];   // first row of the item
-  int32_t item_rows[kAttnMaxItems];   // rows (1 .. 64)
-  int32_t item_seg[kAttnMaxItems];    // segment of the first row (context length, page table)
-  int32_t item_slots[kAttnMaxItems];  // draft slots after the context that its rows may see
-  int32_t pt_off[kMaxSegs];
   int32_t n_arg_pages;     // with one KV sequence in the step: valid entries of pages[] (else 0)
+  // per item, 32-bit so that the kernel reads them with scalar loads, and next
+  // to each other, so that it reads one line of the argument block
+  struct Item {
+    int32_t row0;          // first row of the item
+    int32_t rows;          // rows (1 .. 64)
+    int32_t seg;           // segment of the first row (context length, page table)
+    int32_t slots;         // draft slots after the context that its rows may see
+  } item[kAttnMaxItems];
+  int32_t pt_off[kMaxSegs];
   int32_t pages[kArgPages];  // physical ids of that sequence's first pages
 };
 
-struct EmbedArgs {
-  StepParams sp;           // this step's parameters (by value) ...
-  StepParams* sp_dev;      // ... copied here for the later kernels of the step
+struct alignas(64) EmbedArgs {
   const void* embed;       // [V][d] T
   // when set, row m starts from a saved residual instead of its token's
   // embedding: src_h[j][d] fp32 with j = m's local node (a step that resumes
   // after blocks every segment shares with the dense verifier)
   const float* src_h;
-  const float* gain[kMaxSegs];   // per segment: gain of the first RMSNorm its rows meet
   float* h;                // [Mp][d]
   void* xn;                // [Mp][d] activation planes
-  size_t xn_plane;
   float* ss_out;           // [M][ss_stride]: sums of h^2 over 16-column parts
   int ss_stride;
   int d, M;
+  int n_counters;
+  size_t xn_plane;
+
+  StepParams* sp_dev;      // this step's parameters (sp) are copied here for the later kernels of the step
+  StepRows* rows_dev;      // every row's position and physical KV slot, written here
   int32_t* attn_split;     // the attention split report (AttnArgs::split_out): its item count is cleared
   int32_t* counters;       // arrival counters of the step's merges (attention, K split), cleared here
-  int n_counters;
-  StepRows* rows_dev;      // every row's position and physical KV slot, written here
   const int32_t* page_table;
   int32_t pt_off[kMaxSegs];  // each segment's sequence's pages in it
+  const float* gain[kMaxSegs];   // per segment: gain of the first RMSNorm its rows meet
+  StepParams sp;           // this step's parameters (by value)
 };
 
 struct AcceptArgs {
