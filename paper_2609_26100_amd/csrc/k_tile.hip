@@ -533,8 +533,8 @@ static hipError_t tile_go(const GemmArgs& a, hipStream_t s) {
 // those of up to 128 rows; steps: exact row tiles for the residual projections
 // (a K split's partial tiles grow with the rows), 6 or 8 for the others.
 #define TSS_TILES_LARGE(F, E, P)  \
-  F(16, 16, 2, 4, 1, 4, E, P)     \
-  F(16, 8, 4, 2, 1, 5, E, P)      \
+  F(16, 16, 2, 4, 2, 2, E, P)     \
+  F(16, 8, 4, 2, 2, 3, E, P)      \
   F(8, 8, 2, 4, 2, 4, E, P)
 #define TSS_TILES_QKV(F, E, P)    \
   F(6, 3, 2, 3, 2, 6, E, P)       \
