@@ -190,7 +190,8 @@ int tss_set_skip_mask(tss_ctx* ctx, int32_t seq, const uint8_t* mask);
  * computed and kept for every layer the mask runs.  The tokens go through the
  * decoder in chunks of min(64, rows of one step); in the TSS_BF16 mode more
  * tokens than one such chunk go through it in passes of up to 2048 tokens,
- * whose buffers lie in the KV pool.  TSS_ECAPACITY past the
+ * whose buffers lie behind the pages of the KV pool (a pool bound with room
+ * for the pages alone takes them in chunks).  TSS_ECAPACITY past the
  * sequence's capacity, TSS_ESTATE if an active layer lacks K/V for the
  * committed context.  Paper: Method / Domain-Aware Skip Controller (the same
  * block rule in the target's forward for every token of the request). */

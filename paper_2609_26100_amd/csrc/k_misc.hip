@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void k_embed(EmbedArgs a) {
     for (int i = threadIdx.x; i < a.n_counters; i += 256) a.counters[i] = 0;
     // each row's position and physical KV slot
     const int r = (int)threadIdx.x - (256 - kMaxRows);
-    if (r >= 0 && r < a.M) {
+    if (a.rows_dev && r >= 0 && r < a.M) {
       const int sq = a.sp.row_seq[r], nkv = a.sp.seq_nkv[sq];
       const int slot = nkv + a.sp.seg_slot0[sq] + r - a.sp.seq_row0[sq];
       a.rows_dev->pos[r] = nkv + a.sp.depth[r];

@@ -192,7 +192,8 @@ WsLayout ws_layout(const tss_model_cfg* c) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   w.sp = take(sizeof(StepParams));
-  w.rows = take(sizeof(StepRows));
+  // only steps of more than 64 rows read it (k_tile's Q/K/V)
+  w.rows = Mp > 64 ? take(sizeof(StepRows)) : 0;
   w.result = take(kMaxSegs * sizeof(Result));
   w.h = take(Mp * d * 4);
   w.xa = take(ap * Mp * d * es);
@@ -232,6 +233,7 @@ struct KvLayout {
   // residual, projection input (of either norm), q and attention output or
   // the SwiGLU output, norm partial sums, K-split partial tiles and counters
   int prompt_rows = 0;
+  size_t pages_end = 0;  // end of the pages
   size_t p_h = 0, p_x = 0, p_q = 0, p_o = 0, p_act = 0, p_ss = 0, p_parts = 0, p_count = 0, parts_bytes = 0;
 };
 
@@ -244,6 +246,7 @@ KvLayout kv_layout(const tss_model_cfg* c, int n_seqs, int max_tokens) {
   k.page_table = take((size_t)k.n_pages * 4);
   k.rope = take((size_t)max_tokens * (c->head_dim / 2) * sizeof(float2));
   k.pages = take((size_t)c->n_layers * k.n_pages * 2 * c->n_heads * kPage * c->head_dim * elem_size(c));
+  k.pages_end = off;
   // a prompt that one small step takes needs no pass
   if (c->dtype == TSS_BF16 && max_tokens > std::min(kMaxNodes, row_cap(c))) {
     const size_t d = c->d_model, f = c->ffn_dim;
@@ -695,8 +698,9 @@ int tss_kv_alloc(tss_ctx* c, int32_t n_seqs, int32_t max_tokens_per_seq, void* d
   if (!c) return TSS_EINVAL;
   if (c->poisoned) return fail(c, TSS_ESTATE, "context poisoned by an earlier HIP error");
   if (n_seqs < 1 || max_tokens_per_seq < 1 || !dev_pool) return fail(c, TSS_EINVAL, "bad KV pool arguments");
-  const KvLayout k = kv_layout(&c->cfg, n_seqs, max_tokens_per_seq);
-  if (pool_bytes < k.total) return fail(c, TSS_ENOSPACE, "KV pool smaller than tss_kv_bytes()");
+  KvLayout k = kv_layout(&c->cfg, n_seqs, max_tokens_per_seq);
+  if (pool_bytes < k.pages_end) return fail(c, TSS_ENOSPACE, "KV pool smaller than tss_kv_bytes()");
+  if (pool_bytes < k.total) k.prompt_rows = 0;  // room for the pages alone: prompts go in small steps
   std::vector<int32_t> pt(k.n_pages);
   if (page_order) {
     std::vector<uint8_t> seen(k.n_pages, 0);
@@ -1288,7 +1292,7 @@ EmbedArgs embed_args(tss_ctx* c, int start_layer, const float* src_h) {
   a.attn_split = (int32_t*)(c->ws + c->wsl.attn_split);
   a.counters = (int32_t*)(c->ws + c->wsl.counters);
   a.n_counters = c->wsl.n_counters;
-  a.rows_dev = (StepRows*)(c->ws + c->wsl.rows);
+  a.rows_dev = c->wsl.rows ? (StepRows*)(c->ws + c->wsl.rows) : nullptr;
   a.page_table = (const int32_t*)(c->kv + c->kvl.page_table);
   for (int i = 0; i < c->step.n_seqs; ++i) a.pt_off[i] = c->step.seq[i] * c->kvl.pages_per_seq;
   return a;

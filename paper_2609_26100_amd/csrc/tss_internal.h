@@ -180,9 +180,10 @@ enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 // Kernel arguments are read a 64-byte line at a time, each first touch a round
 // trip to the argument block, so the fields stand in the order of their use:
 // what the prologue needs in the first two lines, what the epilogues need in
-// the next two, the long arrays behind (7B one-node step 415 -> 408 us, k = 5
-// step 428 -> 424, with the kernels' own first touches of the epilogue lines
-// behind the weight ring's first loads).
+// the next two, the long arrays behind (with the kernels' own first touches of
+// the epilogue lines behind the weight ring's first loads: tiny decoder's
+// projections 0.2-0.4 us a launch, 7B k = 5 step 428 -> 424 us, batch of four 526
+// -> 524, one-node step between 415 -> 408 and no change over two pairs of runs).
 struct alignas(64) GemmArgs {
   const uint8_t* w;        // packed weights of this matrix
   const void* x;           // A operand [Mp][K] of T in tile order (act_index)

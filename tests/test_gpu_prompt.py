@@ -100,3 +100,31 @@ def test_every_block_skipped_keeps_the_length(model):
     v.set_mask(0, None)
     with pytest.raises(Exception, match="lacks K/V"):
         v.prefill(0, synth.context_tokens(shape.vocab, 100, stream=9))
+
+
+def test_long_prompt_and_a_pool_without_room_for_passes():
+    """4400 tokens in three passes (the last rows walk more than 64 steps of four pages) against the same
+    prompt on a pool whose bytes hold the pages alone, which takes it in small steps."""
+    import torch
+    from paper_2609_26100_amd import tss as abi
+    shape = synth.ModelShape("prompt-long", 97, n_layers=2, d_model=256, n_heads=2, head_dim=128, ffn_dim=352, vocab=416,
+                             dtype="bf16")
+    toks = synth.context_tokens(shape.vocab, 4400, stream=11)
+    draft = synth.context_tokens(shape.vocab, 6, stream=12)
+    out = []
+    for small in (False, True):
+        v = gpu_verifier(shape, n_seqs=1, max_tokens=4480, max_nodes=16)
+        if small:
+            pages = 280
+            need = pages * 4 + 4480 * 64 * 8 + 2 * pages * 2 * 2 * 16 * 128 * 2 + 3 * 256
+            assert need < abi.tss_kv_bytes(v.cfg, 1, 4480)
+            pool = torch.zeros(need, dtype=torch.uint8, device="cuda:0")
+            torch.cuda.synchronize()
+            abi.tss_kv_alloc(v.ctx, 1, 4480, pool.data_ptr(), need)
+        v.prefill(0, toks)
+        assert v.length(0) == 4400
+        v.verify(0, draft)
+        out.append(v.logits(6))
+        v.close()
+    log(f"4400 tokens: passes against small steps {_rel(out[0], out[1]):.2e}")
+    assert _rel(out[0], out[1]) <= REL
