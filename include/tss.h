@@ -168,7 +168,8 @@ int tss_create(const tss_model_cfg* cfg, void* hip_stream, void* dev_weights, si
 int tss_load_weights(tss_ctx* ctx, int32_t first, int32_t count, const void* const* host_tensors);
 
 /* Binds a KV pool of tss_kv_bytes(cfg, n_seqs, max_tokens_per_seq) bytes of
- * device memory and resets every sequence to length 0 (masks to dense).
+ * device memory, clears its pages (the caller's bytes there may be anything)
+ * and resets every sequence to length 0 (masks to dense).
  * page_order, if not NULL, lists a permutation of the pool's
  * n_seqs * ceil(max_tokens/16) pages; sequence s owns the s-th run of pages
  * in that order (NULL = identity); TSS_EINVAL if it is not a permutation.

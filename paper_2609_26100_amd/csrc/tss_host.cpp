@@ -724,7 +724,10 @@ int tss_kv_alloc(tss_ctx* c, int32_t n_seqs, int32_t max_tokens_per_seq, void* d
   HIPCHK(launch_rope_table((float2*)(c->kv + k.rope), max_tokens_per_seq, c->cfg.head_dim, c->cfg.rope_base,
                            c->stream),
          "rope table");
-  HIPCHK(hipStreamSynchronize(c->stream), "rope table");
+  // A masked key has probability 0, but its V still enters the product, where
+  // 0 * NaN is NaN: slots that no token has filled must hold finite values
+  HIPCHK(hipMemsetAsync(c->kv + k.pages, 0, k.pages_end - k.pages, c->stream), "clearing the pages");
+  HIPCHK(hipStreamSynchronize(c->stream), "rope table and cleared pages");
   c->n_kv.assign(n_seqs, 0);
   c->kv_len.assign(n_seqs, std::vector<int32_t>(c->cfg.n_layers, 0));
   c->mask.assign(n_seqs, std::vector<uint8_t>(c->cfg.n_layers, 0));
