@@ -1,7 +1,8 @@
 """Prefill passes of many tokens (bf16 mode) at the sizes where their tiling can go wrong: one token past
-what a small step takes, the edges of the 16-, 128- and 256-row blocks, more than one pass, a pass that
-starts inside a page, both head dims, widths that no column block divides, skipped first, middle and last
-blocks, permuted pages.  Each prompt's K/V are judged through the logits of the steps that read them,
+what a small step takes, the edges of the 16- and 128-row blocks, more than one pass, a pass that starts
+inside a page, both head dims, widths that no column block divides, skipped first, middle and last blocks,
+permuted pages; on wider models (BLOCK_CASES) every block shape of more than 128 rows and the residual
+projections' K splits, with ragged rows, columns and K chunks.  Each prompt's K/V are judged through the logits of the steps that read them,
 against the oracle and against the same prompt prefilled in calls of at most 64 tokens (the small-step
 path).
 
@@ -22,6 +23,32 @@ HD64 = synth.ModelShape("prompt-d320", 91, n_layers=3, d_model=320, n_heads=5, h
                         dtype="bf16")
 HD128 = synth.ModelShape("prompt-d640", 92, n_layers=3, d_model=640, n_heads=5, head_dim=128, ffn_dim=1056, vocab=416,
                          dtype="bf16")
+
+# Models wide enough for every block shape that prompts of more than 128 rows can take: column tiles that 8, 12 or
+# 16 do not divide and an odd number of K chunks of the down projection (65, 131 and 33; d / 32 is always even).
+WIDE = {
+    "d2176": synth.ModelShape("prompt-d2176", 101, n_layers=2, d_model=2176, n_heads=17, head_dim=128, ffn_dim=2080,
+                              vocab=416, dtype="bf16"),
+    "d1088": synth.ModelShape("prompt-d1088", 102, n_layers=2, d_model=1088, n_heads=17, head_dim=64, ffn_dim=4192,
+                              vocab=416, dtype="bf16"),
+    "d4160": synth.ModelShape("prompt-d4160", 103, n_layers=2, d_model=4160, n_heads=65, head_dim=64, ffn_dim=1056,
+                              vocab=416, dtype="bf16"),
+}
+WIDE_MAX_TOKENS = 2112
+# model, prompt rows, and the blocks (row tiles, column tiles, K splits) of Q/K/V, gate/up, O and down;
+# test_tile_shapes.py compares these with the host's rule.  Every row count ends inside a row tile and, but for 2045
+# (13 rows in the last tile of whole blocks), inside a row block.
+BLOCK_CASES = [
+    ("d2176", 137, (8, 8, 1), (8, 8, 1), (8, 8, 4), (8, 4, 3)),
+    ("d2176", 300, (8, 8, 1), (8, 8, 1), (8, 8, 4), (8, 8, 4)),
+    ("d2176", 1030, (16, 8, 1), (16, 8, 1), (8, 8, 1), (8, 8, 1)),
+    ("d2176", 1300, (16, 12, 1), (16, 8, 1), (8, 8, 1), (8, 8, 1)),
+    ("d2176", 2045, (16, 16, 1), (16, 12, 1), (16, 8, 1), (16, 8, 1)),
+    ("d1088", 777, (8, 8, 1), (16, 12, 1), (8, 4, 1), (8, 8, 4)),
+    ("d1088", 1300, (16, 8, 1), (16, 16, 1), (8, 4, 1), (8, 8, 2)),
+    ("d4160", 300, (16, 8, 1), (8, 8, 1), (8, 8, 2), (8, 4, 1)),
+    ("d4160", 2045, (16, 16, 1), (16, 8, 1), (16, 16, 1), (16, 16, 1)),
+]
 
 
 def _rel(a, b):
@@ -128,3 +155,32 @@ def test_long_prompt_and_a_pool_without_room_for_passes():
         v.close()
     log(f"4400 tokens: passes against small steps {_rel(out[0], out[1]):.2e}")
     assert _rel(out[0], out[1]) <= REL
+
+
+@pytest.fixture(scope="module", params=list(WIDE))
+def wide(request):
+    shape = WIDE[request.param]
+    order = np.random.default_rng(13).permutation(2 * ((WIDE_MAX_TOKENS + 15) // 16))
+    v = gpu_verifier(shape, random_gains=True, n_seqs=2, max_tokens=WIDE_MAX_TOKENS, max_nodes=64, page_order=order)
+    yield request.param, shape, v
+    v.close()
+
+
+def test_every_block_shape_at_ragged_sizes(wide):
+    """Two blocks: the first runs whole, the second ends at its K/V, so all four projections of the pass are in the
+    logits.  Against the same prompt in calls of at most 64 tokens, whose kernels other tests compare with the
+    oracle; a repeat gives the same bits."""
+    name, shape, v = wide
+    draft = synth.context_tokens(shape.vocab, 6, stream=20)
+    for n in [c[1] for c in BLOCK_CASES if c[0] == name]:
+        toks = synth.context_tokens(shape.vocab, n, stream=n)
+        out = []
+        for s, step in ((0, n), (0, n), (1, 64)):
+            v.truncate(s, 0)
+            for i in range(0, n, step):
+                v.prefill(s, toks[i:i + step])
+            v.verify(s, draft)
+            out.append(v.logits(6))
+        log(f"{shape.name} {n} rows: against small steps {_rel(out[0], out[2]):.2e}")
+        np.testing.assert_array_equal(out[0], out[1])
+        assert _rel(out[0], out[2]) <= REL

@@ -1,0 +1,54 @@
+"""The host's block-shape rule for prompt projections, evaluated on the CPU: the sizes that test_gpu_prompt.py
+names reach the block shapes that it names, and together every shape a prompt of more than 128 rows can take."""
+import os
+import subprocess
+
+import pytest
+
+from tests.test_gpu_prompt import BLOCK_CASES, WIDE, WIDE_MAX_TOKENS
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+QKV, RESID, SWIGLU = 0, 1, 2  # enum Epi
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("ROCm clang++ not installed")
+    exe = str(tmp_path_factory.mktemp("shapes") / "shapes")
+    cmd = [CLANG, "-std=c++17", "-O1", "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2609_26100_amd", "csrc"),
+           "-Wno-everything", os.path.join(ROOT, "tests", "host_shapes", "shapes.cpp"),
+           "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def shapes(which, projections):
+        args = [str(x) for p in projections for x in p]
+        r = subprocess.run([exe, which, *args], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr
+        return [tuple(int(x) for x in line.split()) for line in r.stdout.splitlines()]
+    return shapes
+
+
+def prompt_shapes(rule, s, rows, max_tokens):
+    """Blocks of a pass's Q/K/V, gate/up, O and down projections (partial tiles: as the KV pool has room for them)."""
+    cap = min(2048, -(-max_tokens // 16) * 16)
+    parts = min(16 << 20, 4 * (-(-cap // 256) * 256) * (-(-s.d_model // 256) * 256) * 4)
+    rt, d, f = -(-rows // 16), s.d_model, s.ffn_dim
+    return rule("prompt", [(QKV, rt, 3 * d // 16, d // 32, 0), (SWIGLU, rt, 2 * f // 16, d // 32, 0),
+                           (RESID, rt, d // 16, d // 32, parts), (RESID, rt, d // 16, f // 32, parts)])
+
+
+@pytest.mark.parametrize("case", BLOCK_CASES, ids=lambda c: f"{c[0]}-{c[1]}")
+def test_the_sizes_reach_the_named_blocks(rule, case):
+    assert tuple(prompt_shapes(rule, WIDE[case[0]], case[1], WIDE_MAX_TOKENS)) == tuple(case[2:])
+
+
+def test_the_cases_cover_every_large_block():
+    large, resid = {(16, 16), (16, 12), (16, 8), (8, 8)}, {(16, 16), (16, 8), (8, 8), (8, 4)}
+    for i in (2, 3):
+        assert {c[i][:2] for c in BLOCK_CASES} == large
+    assert {c[i][:2] for c in BLOCK_CASES for i in (4, 5)} == resid
+    assert {c[i][2] for c in BLOCK_CASES for i in (4, 5)} == {1, 2, 3, 4}  # K splits
