@@ -108,6 +108,19 @@ __device__ __forceinline__ float4 load_agent4(__amdgpu_buffer_rsrc_t r, int off)
 #endif
 constexpr int kAttnWaves = TSS_ATTN_WAVES;
 
+// Whether a row sees a slot: every slot of the context, and past it the draft
+// slots (node j at slot node0 + j) whose bit is set in the row's anc.  Without
+// branches on purpose.  Written with && and ||, `vis ? S : -INFINITY` becomes a
+// three-way phi whose register this image's compiler (AMD clang 22.0.0git of
+// ROCm 7.2.0) shares with the MFMA's result S: the AMD assembly writes -inf to
+// it in every lane past the context, and the block that should keep S for the
+// visible ones is empty, although the optimised IR before it is right.  Trees
+// then lost every draft key.
+__device__ __forceinline__ bool slot_visible(int slot, int n_kv, int node0, uint64_t anc) {
+  const unsigned j = (unsigned)(slot - node0);
+  return (slot < n_kv) | ((j < 64u) & (bool)((anc >> (j & 63u)) & 1ull));
+}
+
 // Workgroups an item's n_pages pages are divided among: at most `groups`, at
 // least a page per wave, few enough that the partial states (T tiles each)
 // stay well below the pages, and in a batch of sequences one per
@@ -334,14 +347,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void k_attn(AttnArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int slot = pg * kPage + grp * 4 + v;
-          bool vis;
-          if (slot < n_kv) {
-            vis = true;
-          } else {
-            const unsigned j = (unsigned)(slot - n_kv - base[t]);
-            vis = j < 64u && ((anc[t] >> j) & 1ull);
-          }
-          s[v] = vis ? S[v] * a.scale_log2 : -INFINITY;
+          s[v] = slot_visible(slot, n_kv, base[t] + n_kv, anc[t]) ? S[v] * a.scale_log2 : -INFINITY;
           mloc = fmaxf(mloc, s[v]);
         }
       }
@@ -750,12 +756,7 @@ __global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
       for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int slot = s0 + p * kPage + v;
-          const unsigned j = (unsigned)(slot - base);
-          // without short-circuit: lanes differ (and with it this compiler
-          // hid the visible draft slots too)
-          const bool vis = (slot < n_kv) | ((j < 64u) & (bool)((anc >> (j & 63u)) & 1ull));
-          S[p][v] = vis ? S[p][v] : -INFINITY;
+          S[p][v] = slot_visible(s0 + p * kPage + v, n_kv, base, anc) ? S[p][v] : -INFINITY;
         }
     }
     float mx = -INFINITY;

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kPaWaves * 64, 2) void k_prompt_attn(PromptAttnArgs
           for (int p = 0; p < kPaPages; ++p)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-              if (tok0 + p * 16 + v > pos + r16) S[p][v] = -INFINITY;
+              S[p][v] = tok0 + p * 16 + v > pos + r16 ? -INFINITY : S[p][v];  // a select, no branch
         }
         float mx = -INFINITY;
 #pragma unroll
