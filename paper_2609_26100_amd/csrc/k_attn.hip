@@ -677,10 +677,7 @@ __global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
         a.kv_pages + ((((size_t)a.layer * a.n_pages_pool + phys) * 2 + kv) * a.n_heads + head) * blk;
     const unsigned dst = lds0 + (unsigned)(slot * STAGE + (pg_w * 2 + kv) * NK * 1024);
 #pragma unroll
-    for (int c = 0; c < NK; ++c)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + c * 1024u),
-                   "v"(off + c * off_step), "s"(b)
-                   : "memory");
+    for (int c = 0; c < NK; ++c) dma_kib(b, off + c * off_step, dst + c * 1024u);
   };
   // this wave's page of the workgroup's k-th step
   auto page = [&](int k) { return (g + k * stride) * kTreePages + pg_w; };

@@ -96,15 +96,9 @@ __global__ __launch_bounds__(kPaWaves * 64, 2) void k_prompt_attn(PromptAttnArgs
     const uint8_t* vb = kb + (size_t)a.n_heads * blk * 2;
     const unsigned dst = lds0 + (unsigned)((st % kPaStages) * STAGE + wave * 2 * NK * 1024);
 #pragma unroll
-    for (int c = 0; c < NK; ++c)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + c * 1024u),
-                   "v"(koff + c * 64u), "s"(kb)
-                   : "memory");
+    for (int c = 0; c < NK; ++c) dma_kib(kb, koff + c * 64u, dst + c * 1024u);
 #pragma unroll
-    for (int c = 0; c < NK; ++c)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst + (NK + c) * 1024u),
-                   "v"(voff + c * 256u), "s"(vb)
-                   : "memory");
+    for (int c = 0; c < NK; ++c) dma_kib(vb, voff + c * 256u, dst + (NK + c) * 1024u);
   };
 
   // q tiles: lane (row r16, group grp) holds dims 32 c + 8 grp .. + 7 of its row

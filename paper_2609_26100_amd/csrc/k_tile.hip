@@ -46,17 +46,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-// One KiB from global memory (g + each lane's off) into LDS (uniform byte
-// offset lds of the workgroup's LDS): lane l's 16 bytes land at lds + 16 * l.
-// The builtin for this load makes the compiler wait for every load in flight
-// before any later LDS read, which would empty the ring each stage; the
-// kernel's own counted waits and barriers order these loads instead.  The
-// asm writes no register but m0, which nothing else here uses.
-__device__ __forceinline__ void dma_kib(const uint8_t* g, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(g)
-               : "memory");
-}
-
 // At most N of this wave's vector memory operations outstanding, and all its
 // LDS reads done (the slot it has read may be refilled after the barrier).
 template <int N>

@@ -101,6 +101,24 @@ __device__ __forceinline__ size_t act_index(int row, int k, int K) {
   return (((size_t)(row >> 4) * nkc + k / KC) * 64 + (k % KC) / KL * 16 + (row & 15)) * KL + (k % KL);
 }
 
+#ifdef __HIPCC__
+// One KiB from global memory (g + each lane's off) into LDS (uniform byte
+// offset lds of the workgroup's LDS): lane l's 16 bytes land at lds + 16 * l.
+// The builtin for this load makes the compiler wait for every load in flight
+// before any later LDS read, which would empty a ring each stage; the kernels'
+// own counted waits and barriers order these loads instead.  The asm writes no
+// register but m0.  The compiler reserves m0 (no value of its own stays there)
+// and warns about the clobber, which keeps the asm from being moved between
+// another write of m0 and the instruction that it is for.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma_kib(const uint8_t* g, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(g)
+               : "memory", "m0");
+}
+#pragma clang diagnostic pop
+#endif
+
 // Stores an fp32 activation in the mode's plane format.
 template <typename T>
 __device__ __forceinline__ void store_act(void* base, size_t plane, size_t idx, float v) {
