@@ -120,9 +120,11 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
 // the store has landed) runs one accept scan per sequence over its tree: a
 // node is accepted when its parent is and its token equals the parent's
 // greedy token; the deepest accepted node (lowest id among equal depths)
-// gives accept_len and the bonus token.  One wave takes a sequence, one lane a
-// node (one thread walking the nodes took most of a 61-node launch: 10.8 ->
-// 6.5 us).
+// gives accept_len and the bonus token.  One thread takes a row, so all
+// sequences are scanned at once.  Traced launches, one thread walking the
+// nodes of each sequence / one wave for each sequence in turn / this: one tree
+// of 61 nodes 10.9 / 6.5 / 6.4 us, 15 drafts of 8 nodes 6.6 / 8.4 / 6.2, 8 of 9
+// nodes 6.7 / 7.3 / 6.1, 4 of 6 nodes 5.9 / 6.0 / 5.7.
 constexpr int kAcceptThreads = 256;
 constexpr int kAcceptLoads = 8;  // partials per thread per round (2048 per round: V = 32000 in one)
 __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
@@ -130,24 +132,24 @@ __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
   __shared__ int32_t bis[kAcceptThreads / 64];
   __shared__ int last;
   __shared__ int32_t g[kMaxRows];
-  __shared__ int32_t s_tok[kMaxRows];
-  __shared__ int8_t s_par[kMaxRows];
-  __shared__ uint8_t s_dep[kMaxRows];
   __shared__ uint64_t s_anc[kMaxRows];
-  __shared__ int s_row0[kMaxSegs + 1];
+  __shared__ uint64_t s_match[kMaxRows / 64];
+  __shared__ int s_row0[kMaxSegs];
+  __shared__ int s_key[kMaxSegs];
   const int m = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int M = a.M;
-  // what the scan needs beside the greedy tokens, by every workgroup (any may
-  // be the last): on its way while the partials are reduced
-  for (int i = threadIdx.x; i < M; i += kAcceptThreads) {
-    s_tok[i] = a.sp->tok[i];
-    s_par[i] = a.sp->parent[i];
-    s_dep[i] = a.sp->depth[i];
-    s_anc[i] = a.sp->anc[i];
-  }
-  const int n_seqs = a.sp->n_seqs;
-  if (threadIdx.x <= n_seqs) s_row0[threadIdx.x] = a.sp->seq_row0[threadIdx.x];
+  // What the scan needs beside the greedy tokens, by every workgroup (any may
+  // be the last), one row and one segment a thread: requested ahead of the
+  // partials and used behind their reduction, so it costs no round trip of its
+  // own.  Past the step's rows and segments the arrays hold their own unused
+  // entries.
+  static_assert(kMaxRows % 64 == 0 && kMaxRows <= kAcceptThreads && kMaxSegs <= kAcceptThreads, "one entry per thread");
+  const int ri = min((int)threadIdx.x, kMaxRows - 1), si = min((int)threadIdx.x, kMaxSegs - 1);
+  const int32_t tok = a.sp->tok[ri];
+  const int par = a.sp->parent[ri], dep = a.sp->depth[ri], seg = a.sp->row_seq[ri];
+  const uint64_t anc = a.sp->anc[ri];
+  const int seg_row0 = a.sp->seq_row0[si];
   // the row's partials through buffer resources: loads past the row return
   // zeros (replaced below), so none needs a branch
   const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
@@ -187,6 +189,11 @@ __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
     bvs[wave] = bv;
     bis[wave] = bi;
   }
+  if (threadIdx.x < kMaxRows) s_anc[ri] = anc;
+  if (threadIdx.x < kMaxSegs) {
+    s_row0[si] = seg_row0;
+    s_key[si] = 0;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < kAcceptThreads / 64; ++w)
@@ -204,30 +211,35 @@ __global__ __launch_bounds__(kAcceptThreads) void k_accept(AcceptArgs a) {
   for (int i = threadIdx.x; i < M; i += kAcceptThreads)
     g[i] = __hip_atomic_load(a.greedy + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  // one wave per segment, one lane per node: a node is accepted when it and
+  // every segment at once, one thread per row: a node is accepted when it and
   // every ancestor match the greedy token of their parents
-  for (int sq = wave; sq < n_seqs; sq += kAcceptThreads / 64) {
-    const int r0 = s_row0[sq], n = s_row0[sq + 1] - r0;
-    const int32_t* gs = g + r0;
-    const bool node = lane < n;
-    const int r = r0 + (node ? lane : 0);
-    const uint64_t matched = __ballot(node && (lane == 0 || s_tok[r] == gs[max((int)s_par[r], 0)]));
-    // deepest accepted node, lowest id among equal depths (the root always is)
-    int key = node && (s_anc[r] & ~matched) == 0 ? (s_dep[r] << 8) | (255 - lane) : 255;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
-    const int best = 255 - (key & 255), len = key >> 8;
-    const bool on_path = (s_anc[r0 + best] >> lane) & 1ull;
+  const bool on = (int)threadIdx.x < M;  // M <= kMaxRows
+  const int r0 = on ? s_row0[seg] : 0, local = on ? ri - r0 : 0;
+  const uint64_t match = __ballot(on && (local == 0 || tok == g[r0 + max(par, 0)]));
+  if (lane == 0 && wave < kMaxRows / 64) s_match[wave] = match;
+  __syncthreads();
+  // deepest accepted node, lowest id among equal depths (the root always is)
+  if (on) {
+    static_assert(kMaxRows == 128, "two words of rows");
+    const uint64_t lo = s_match[0], hi = s_match[1];
+    const int sh = r0 & 63;
+    const uint64_t seg_match = r0 >= 64 ? hi >> sh : (sh ? (lo >> sh) | (hi << (64 - sh)) : lo);
+    if ((anc & ~seg_match) == 0) atomicMax(&s_key[seg], (dep << 8) | (255 - local));
+  }
+  __syncthreads();
+  if (on) {
+    const int key = s_key[seg], best = 255 - (key & 255), len = key >> 8;
+    const bool on_path = (s_anc[r0 + best] >> local) & 1ull;
 #pragma unroll
     for (int copy = 0; copy < 2; ++copy) {
-      Result* res = (copy == 0 ? a.result : a.result_host) + sq;
-      if (lane == 0) {
+      Result* res = (copy == 0 ? a.result : a.result_host) + seg;
+      if (local == 0) {
         res->accept_len = len;
-        res->next_token = gs[best];
+        res->next_token = g[r0 + best];
         res->best = best;
         res->path_len = len + 1;
       }
-      if (on_path) res->path[s_dep[r]] = lane;
+      if (on_path) res->path[dep] = local;
     }
   }
   if (threadIdx.x == 0) *a.count = 0;
