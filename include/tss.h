@@ -367,11 +367,12 @@ int tss_profile_read(tss_ctx* ctx, double* total_ms, int64_t* count, int32_t res
 
 /* How the last step (verify, sweep step or prefill chunk) divided the
  * attention of its last launched block: *n_items attention items (runs of at
- * most 64 consecutive rows of one KV sequence), and for item i the number of
- * workgroups per head its context pages were split among (groups[i]; 1 = no
- * cross-workgroup merge) and its rows (rows[i]).  groups and rows must hold
- * 16 entries (a prefill pass of more rows reports 16 items).
- * *n_items = 0 when the step launched no attention.  Waits for the
+ * most 64 consecutive rows of one KV sequence, 128 in a prefill pass of more
+ * rows than one step takes), and for item i the number of workgroups per head
+ * its context pages were split among (groups[i]; 1 = no cross-workgroup merge)
+ * and its rows (rows[i]).  groups and rows must hold 16 entries.
+ * *n_items = 0 when the step launched no attention (a prefill pass launches
+ * none for the last block that its mask runs).  Waits for the
  * context's stream.  Inspection only (tests assert with it which attention
  * path a launch took); no passage of the paper. */
 int tss_get_attn_split(tss_ctx* ctx, int32_t* n_items, int32_t* groups, int32_t* rows);

@@ -21,11 +21,7 @@ __global__ __launch_bounds__(256) void k_prompt_embed(PromptEmbedArgs a) {
   const int m = a.row0 + blockIdx.x, d = a.d;
   if (m == 0) {
     for (int i = threadIdx.x; i < kPromptCounters; i += 256) a.counters[i] = 0;
-    if (threadIdx.x < kAttnMaxItems) {
-      a.attn_split[threadIdx.x] = 1;
-      a.attn_split[kAttnMaxItems + threadIdx.x] = (int)threadIdx.x == a.split_items - 1 ? a.split_last : 64;
-    }
-    if (threadIdx.x == 0) a.attn_split[2 * kAttnMaxItems] = a.split_items;
+    if (threadIdx.x == 0) a.attn_split[2 * kAttnMaxItems] = 0;
   }
   const _Float16* row = (const _Float16*)a.embed + (size_t)a.tok[blockIdx.x] * d;
   for (int k = threadIdx.x * 4; k < d; k += 1024) {  // d is a multiple of 16, so a part's four lanes stay together
@@ -60,6 +56,7 @@ __global__ __launch_bounds__(256) void k_prompt_embed(PromptEmbedArgs a) {
 // Row blocks are numbered from the last one (the longest walk) down.
 constexpr int kPaWaves = 4, kPaTiles = 2, kPaPages = 4, kPaStages = 2;
 constexpr int kPaRows = kPaWaves * kPaTiles * 16;
+static_assert(kPromptRows <= kAttnMaxItems * kPaRows, "one report item per row block");
 template <int HD>
 constexpr size_t pa_lds() { return (size_t)kPaStages * kPaPages * HD * 64; }
 
@@ -77,6 +74,11 @@ __global__ __launch_bounds__(kPaWaves * 64, 2) void k_prompt_attn(PromptAttnArgs
   const int last = min(rb + kPaRows, M) - 1;                   // last row of the block
   const int n_pages = ((n0 + last) >> 4) + 1;
   const int n_st = (n_pages + kPaPages - 1) / kPaPages;
+  if (head == 0 && threadIdx.x == 0) {  // the split this launch took (inspection)
+    a.split_out[rb / kPaRows] = 1;
+    a.split_out[kAttnMaxItems + rb / kPaRows] = last + 1 - rb;
+    if (rb == 0) a.split_out[2 * kAttnMaxItems] = (int)gridDim.y;
+  }
   const int wrow = rb + wave * kPaTiles * 16;                  // first row of the wave
   // steps that some row of the wave sees (none for a wave past the last row)
   const int my_st = wrow < M ? (((n0 + min(wrow + kPaTiles * 16, M) - 1) >> 4) / kPaPages) + 1 : 0;

@@ -1122,7 +1122,6 @@ int enqueue_prompt(tss_ctx* c, int seq, const int32_t* tokens, int M, int pos0) 
   c->cur_stream = s;
   c->prof_armed = false;
   const int first = next_active(c, 0, -1);
-  if (first == L) return TSS_OK;  // every block skipped: no K/V to compute
   int last = first;
   for (int l = next_active(c, 0, first); l < L; l = next_active(c, 0, l)) last = l;
   const int rt = (M + 15) / 16;
@@ -1142,11 +1141,7 @@ int enqueue_prompt(tss_ctx* c, int seq, const int32_t* tokens, int M, int pos0) 
     a.d = d;
     a.row0 = r0;
     a.counters = counters;
-    // the report names the pass's last 64-row runs, one workgroup each (none when no attention runs)
-    const int items = (M + 63) / 64;
     a.attn_split = (int32_t*)(c->ws + c->wsl.attn_split);
-    a.split_items = first == last ? 0 : std::min(items, kAttnMaxItems);
-    a.split_last = M - (items - 1) * 64;
     ProfScope ps(c, TSS_K_EMBED, -1);
     HIPCHK(launch_prompt_embed(a, rows, s), "prompt embed");
     ps.done();
@@ -1196,6 +1191,7 @@ int enqueue_prompt(tss_ctx* c, int seq, const int32_t* tokens, int M, int pos0) 
       a.kv_pages = c->kv + kl.pages;
       a.page_table = pt;
       a.o = c->kv + kl.p_o;
+      a.split_out = (int32_t*)(c->ws + c->wsl.attn_split);
       a.M = M;
       a.n0 = pos0;
       a.layer = l;

@@ -354,8 +354,7 @@ struct PromptEmbedArgs {
   float* ss_out;           // [M][ss_stride]: sums of h^2 over 16-column parts
   int ss_stride, d, row0;  // row0: row of tok[0]
   int32_t* counters;       // cleared by the launch of row 0
-  int32_t* attn_split;     // the attention split report, written by the launch of row 0
-  int split_items, split_last;  // its items (64 rows each, the last one split_last rows)
+  int32_t* attn_split;     // the attention split report: its item count is cleared by the launch of row 0
 };
 
 struct PromptAttnArgs {
@@ -363,6 +362,7 @@ struct PromptAttnArgs {
   const uint8_t* kv_pages;
   const int32_t* page_table;  // the sequence's pages
   void* o;                 // attention output, act_index order
+  int32_t* split_out;      // report of the launch's split (as AttnArgs::split_out)
   int M, n0, layer, n_pages_pool, n_heads, d;
   float scale_log2;        // log2(e) / sqrt(hd)
 };

@@ -184,3 +184,20 @@ def test_every_block_shape_at_ragged_sizes(wide):
         log(f"{shape.name} {n} rows: against small steps {_rel(out[0], out[2]):.2e}")
         np.testing.assert_array_equal(out[0], out[1])
         assert _rel(out[0], out[2]) <= REL
+
+
+def test_split_report_of_prefill_passes(model):
+    """The report describes the pass's last attention launch: one workgroup a head for each 128 rows; no items when
+    the pass launches no attention (one running block, whose K/V are all that is kept, or none)."""
+    shape, v, m = model
+    toks = synth.context_tokens(shape.vocab, 300, stream=21)
+    for skip, want in (([], [(1, 128), (1, 128), (1, 44)]), ([0, 2], []), ([], [(1, 128), (1, 128), (1, 44)]),
+                       ([0, 1, 2], [])):
+        v.truncate(0, 0)
+        v.set_mask(0, synth.mask_from_layers(shape.n_layers, skip))
+        v.prefill(0, toks)
+        assert v.attn_split() == want, skip
+    v.truncate(0, 0)
+    v.set_mask(0, None)
+    v.prefill(0, synth.context_tokens(shape.vocab, 2240, stream=22))  # two passes: 1280 and 960 rows
+    assert v.attn_split() == [(1, 128)] * 7 + [(1, 64)]
