@@ -353,8 +353,10 @@ int tss_tree_meta(const int32_t* parent, int32_t n_nodes, int32_t* depth, uint64
  * Runtime plumbing; no passage of the paper. */
 int tss_set_launch_mode(tss_ctx* ctx, int32_t mode);
 
-/* Times one kernel launch per verify: the launch of kind `kernel` (enum
- * tss_kernel) for layer `layer` (ignored for kinds outside the layer loop);
+/* Times one kernel launch per verify, and per pass or small step of a prefill
+ * (the first of its kind where a pass takes several): the launch of kind
+ * `kernel` (enum tss_kernel) for layer `layer` (ignored for kinds outside the
+ * layer loop);
  * kernel = -1 switches timing off.  Two HIP events are bound to that launch's
  * own dispatch (hipExtLaunchKernel), so they hold the start and end of the
  * kernel's execution, the figure a kernel-trace profiler reports, with no

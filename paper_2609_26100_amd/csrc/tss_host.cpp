@@ -1651,6 +1651,8 @@ int tss_prefill(tss_ctx* c, int32_t seq, const int32_t* tokens, int32_t n) {
     const int per = std::min(cap, ((n + passes - 1) / passes + 255) / 256 * 256);
     for (int done = 0; done < n; done += per) {
       r = enqueue_prompt(c, seq, tokens + done, std::min(per, n - done), c->n_kv[seq] + done);
+      // a timed launch's events are read before the next pass binds them again
+      if (!r && c->prof_armed) r = finish_step(c);
       if (r) return r;
     }
     r = finish_step(c);
