@@ -79,7 +79,8 @@ enum tss_launch_mode {
 enum tss_kernel {
   TSS_K_EMBED = 0,
   TSS_K_QKV = 1,       /* RMSNorm + Q/K/V projection + rotary + KV append */
-  TSS_K_ATTN = 2,      /* tree-masked attention over the paged KV cache */
+  TSS_K_ATTN = 2,      /* tree-masked attention over the paged KV cache (without the merge launch that
+                          follows it where items have several row tiles) */
   TSS_K_OPROJ = 3,     /* output projection + residual */
   TSS_K_GATEUP = 4,    /* RMSNorm + gate/up projection + SwiGLU */
   TSS_K_DOWN = 5,      /* down projection + residual */

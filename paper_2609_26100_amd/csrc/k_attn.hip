@@ -880,7 +880,8 @@ __global__ __launch_bounds__(kTreeWaves * 64) void k_attn_tree(AttnArgs a) {
 // of the item from its G partial states (plain loads: the attention launch
 // has ended), one thread per four adjacent dimensions of a row, summed in
 // workgroup order; items the attention launch finished itself (G = 1) are
-// skipped.
+// skipped.  Launched outside TSS_LAUNCH: the timing events of an attention
+// launch hold that launch, and bound again they would hold the merge instead.
 constexpr int kMergeRows = 8;
 template <typename TW, int HD, int TMAX, bool TREE = false>
 __global__ __launch_bounds__(kMergeRows * HD / 4) void k_attn_merge(AttnArgs a) {
@@ -977,8 +978,8 @@ static hipError_t attn_t(int n_seq, const AttnArgs& a, hipStream_t s) {
                s, a);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && a.defer_merge) {
-    TSS_LAUNCH((k_attn_merge<TW, HD, TMAX>), dim3(a.n_heads, n_seq, TMAX * 16 / kMergeRows),
-               dim3(kMergeRows * HD / 4), 0, s, a);
+    hipLaunchKernelGGL((k_attn_merge<TW, HD, TMAX>), dim3(a.n_heads, n_seq, TMAX * 16 / kMergeRows),
+                       dim3(kMergeRows * HD / 4), 0, s, a);
     e = hipGetLastError();
   }
   return e;
@@ -989,8 +990,8 @@ static hipError_t attn_tree(int n_items, const AttnArgs& a, hipStream_t s) {
   TSS_LAUNCH(k_attn_tree<HD>, dim3(a.n_heads, n_items, a.groups), dim3(kTreeWaves * 64), tree_lds<HD>(), s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  TSS_LAUNCH((k_attn_merge<_Float16, HD, kAttnMaxTiles, true>),
-             dim3(a.n_heads, n_items, kAttnMaxTiles * 16 / kMergeRows), dim3(kMergeRows * HD / 4), 0, s, a);
+  hipLaunchKernelGGL((k_attn_merge<_Float16, HD, kAttnMaxTiles, true>),
+                     dim3(a.n_heads, n_items, kAttnMaxTiles * 16 / kMergeRows), dim3(kMergeRows * HD / 4), 0, s, a);
   return hipGetLastError();
 }
 
