@@ -109,12 +109,18 @@ __device__ __forceinline__ size_t act_index(int row, int k, int K) {
 // own counted waits and barriers order these loads instead.  The asm writes no
 // register but m0.  The compiler reserves m0 (no value of its own stays there)
 // and warns about the clobber, which keeps the asm from being moved between
-// another write of m0 and the instruction that it is for.
+// another write of m0 and the instruction that it is for.  NT: nontemporal, for
+// bytes that the launch reads once.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+template <bool NT = false>
 __device__ __forceinline__ void dma_kib(const uint8_t* g, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(g)
-               : "memory", "m0");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(g)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(g)
+                 : "memory", "m0");
 }
 #pragma clang diagnostic pop
 #endif
@@ -558,13 +564,15 @@ inline TileShape prompt_tile(int epi, int rt, int ct, int nkc, size_t parts_byte
 // Step projections that k_tile runs (bf16 mode; the others are k_gemm's).
 // What k_gemm's many-row blocks lose to re-reading activations in every wave
 // grows with the rows, and its residual projections sum their waves' partial
-// tiles through LDS before the K split's merge.  In the traced step (us,
-// k_gemm / k_tile): O and down of the 7B shape 13 + 22 / 12 + 21 at 2 row
-// tiles, 16 + 27 / 14 + 26 at 4, 19 + 38 / 18 + 35 at 8, of the 13B shape 21 +
-// 37 / 18 + 39 at 5; with only two K splits (33B) 23 + 49 / 25 + 57 at 3, so
-// those stay up to 5.  8 row tiles: gate/up 69 / 49, Q/K/V 39 / 37, lm_head
-// 89 / 61; 4: 37 / 37, 28 / 27, 53 / 52.  At 5 (13B) lm_head gains (82 / 68) and
-// Q/K/V (40 / 40) and the two-width gate/up (57 / 58) do not.
+// tiles through LDS before the K split's merge.  Traced in models of 6 to 8
+// blocks, whose weights come from HBM in every step (us, k_gemm / k_tile): O
+// and down of the 7B shape 13 + 22 / 12 + 20 at 2 row tiles, 15 + 25 / 13 + 22 at
+// 3, 16 + 27 / 14 + 23 at 4, 18 + 28 / 14 + 25 at 5, 21 + 40 / 18 + 33 at 8, of the
+// 13B shape 16 + 29 / 14 + 27 at 2, 22 + 38 / 19 + 35 at 5; with only two K
+// splits (33B, two blocks) 23 + 49 / 25 + 57 at 3, so those stay up to 5.  7B,
+// 8 row tiles: gate/up 71 / 45, Q/K/V 41 / 34, lm_head 90 / 56; 5: gate/up 56 /
+// 36, lm_head 73 / 48.  At 5 (13B) lm_head gains (82 / 59) and Q/K/V (39 / 40) and
+// the two-width gate/up (57 / 57) do not.
 inline bool step_tiled(bool bf16, int epi, int rt, int N) {
   if (!bf16 || rt < 2) return false;
   if (rt >= 6) return true;
