@@ -205,9 +205,9 @@ enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 // trip to the argument block, so the fields stand in the order of their use:
 // what the prologue needs in the first two lines, what the epilogues need in
 // the next two, the long arrays behind (with the kernels' own first touches of
-// the epilogue lines behind the weight ring's first loads: tiny decoder's
-// projections 0.2-0.4 us a launch, 7B k = 5 step 428 -> 424 us, batch of four 526
-// -> 524, one-node step between 415 -> 408 and no change over two pairs of runs).
+// the epilogue lines behind the weight ring's first loads: 0.2-0.4 us a launch
+// of the tiny decoder's projections in the trace; whole steps change by no more
+// than their runs differ).
 struct alignas(64) GemmArgs {
   const uint8_t* w;        // packed weights of this matrix
   const void* x;           // A operand [Mp][K] of T in tile order (act_index)
@@ -519,11 +519,13 @@ inline int gemm_ksplit(int epi, int mt, int N, int nkc) {
 
 // The cheapest of a projection's block shapes (pairs of MR, NC) for rt row
 // tiles, ct column tiles and nkc K chunks: the one of least estimated time,
-// rounds of 256 workgroups times the chunks of a K split times a chunk's time
-// (0.2 us + 2.7 ns per output tile; measured on the 7B shapes 16 x 16 tiles
-// 0.87-1.0 us, 16 x 12 0.83, 16 x 8 0.53, 8 x 8 0.33, 8 x 6 0.38), plus 8 us
-// where the residual projections split K (parts_bytes: room for the partial
-// tiles).
+// rounds of 256 workgroups times the chunks of a K split times a chunk's time,
+// plus 8 us where the residual projections split K (parts_bytes: room for the
+// partial tiles).  The chunk's time of 0.2 us + 2.7 ns per output tile is a line
+// through measurements on the 7B shapes that lie up to 14 % off it: 16 x 16
+// tiles 0.89 us (measured 0.87-1.0), 16 x 12 0.72 (0.83), 16 x 8 0.55 (0.53), 8 x 8
+// 0.37 (0.33), 8 x 6 0.33 (0.38).  A last round counts as a whole one, also
+// where few of its blocks are left.
 template <int NS>
 inline TileShape cheapest_tile(const int (&shapes)[NS][2], int epi, int rt, int ct, int nkc, size_t parts_bytes,
                                int max_blocks) {
