@@ -580,6 +580,10 @@ static hipError_t tile_go(const GemmArgs& a, hipStream_t s) {
   TSS_TILES_QKV(F, EPI_QKV, false)       \
   TSS_TILES_GATEUP(F, EPI_SWIGLU, false) \
   F(8, 8, 2, 4, 2, 4, EPI_SWIGLU, false) \
+  F(6, 2, 3, 2, 2, 6, EPI_QKV, false)    \
+  F(8, 2, 4, 2, 2, 6, EPI_QKV, false)    \
+  F(6, 4, 3, 2, 2, 6, EPI_SWIGLU, false) \
+  F(8, 4, 4, 2, 2, 6, EPI_SWIGLU, false) \
   TSS_TILES_RESID(F, EPI_RESID, false)   \
   F(2, 4, 2, 4, 2, 8, EPI_RESID, false)  \
   F(3, 4, 3, 2, 2, 8, EPI_RESID, false)  \

@@ -582,10 +582,14 @@ inline bool step_tiled(bool bf16, int epi, int rt, int N) {
   return rt == 5 && (epi == EPI_LOGITS || (epi == EPI_SWIGLU && gemm_wide_pairs(epi, rt, N) == 0));
 }
 
-// Block shape of a step projection that k_tile runs.
+// Block shape of a step projection that k_tile runs.  The two-column Q/K/V and
+// four-column gate/up blocks are for matrices that wider blocks would leave on
+// at most half of the CUs: traced at 128 rows (us, three / two columns and
+// six / four), d 2048 with 5632 FFN rows 19.1 / 15.9 and 22.7 / 19.1, d 1024 with
+// 2816 12.5 / 10.7 and 14.0 / 11.5 (k_gemm 19.4, 21.3, 11.1 and 13.2).
 inline TileShape step_tile(int epi, int rt, int ct, int nkc, size_t parts_bytes = 0) {
-  constexpr int q6[][2] = {{6, 3}, {6, 4}, {6, 6}}, q8[][2] = {{8, 3}, {8, 4}, {8, 6}};
-  constexpr int g6[][2] = {{6, 6}, {6, 8}, {6, 10}}, g8[][2] = {{8, 6}, {8, 8}, {8, 10}};
+  constexpr int q6[][2] = {{6, 2}, {6, 3}, {6, 4}, {6, 6}}, q8[][2] = {{8, 2}, {8, 3}, {8, 4}, {8, 6}};
+  constexpr int g6[][2] = {{6, 4}, {6, 6}, {6, 8}, {6, 10}}, g8[][2] = {{8, 4}, {8, 6}, {8, 8}, {8, 10}};
   auto pick = [&](const auto& sh) { return cheapest_tile(sh, epi, rt, ct, nkc, parts_bytes, ct); };
   if (epi == EPI_LOGITS) return TileShape{rt <= 6 ? 6 : 8, 8, 1};
   if (epi == EPI_QKV) return rt <= 6 ? pick(q6) : pick(q8);

@@ -20,6 +20,18 @@ SMALL = synth.ModelShape("rows-d320", 93, n_layers=2, d_model=320, n_heads=5, he
 SPLIT = synth.ModelShape("rows-d1024", 94, n_layers=2, d_model=1024, n_heads=8, head_dim=128, ffn_dim=2080, vocab=1056,
                          dtype="bf16")
 
+# One-block models wide enough for the other blocks of steps of 6 to 8 row tiles (the two above take the narrowest):
+# model, then the column tiles of its Q/K/V and gate/up blocks, which test_tile_shapes.py compares with the host's
+# rule.  The gate/up columns leave a partial last block.
+WIDE = {
+    "d2752": (synth.ModelShape("rows-d2752", 107, n_layers=1, d_model=2752, n_heads=43, head_dim=64, ffn_dim=8224,
+                               vocab=416, dtype="bf16"), 3, 6),
+    "d4160": (synth.ModelShape("rows-d4160", 108, n_layers=1, d_model=4160, n_heads=65, head_dim=64, ffn_dim=12320,
+                               vocab=416, dtype="bf16"), 4, 8),
+    "d5504": (synth.ModelShape("rows-d5504", 109, n_layers=1, d_model=5504, n_heads=43, head_dim=128, ffn_dim=16416,
+                               vocab=416, dtype="bf16"), 6, 10),
+}
+
 
 def _rel(a, b):
     a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
@@ -130,4 +142,28 @@ def test_tree_attention_of_many_steps_per_workgroup():
             e = _rel(got[k, node], v.logits(len(path))[-1])
             log(f"node {node} depth {len(path) - 1} mask {k}: rel {e:.2e}")
             assert e <= REL
+    v.close()
+
+
+@pytest.mark.parametrize("name", list(WIDE))
+def test_wide_blocks_against_single_verifies(name):
+    """81, 113 and 128 rows (6, 8 and 8 row tiles) of sequences of at most 16 rows, against each sequence's own
+    verify."""
+    shape = WIDE[name][0]
+    v = gpu_verifier(shape, random_gains=True, n_seqs=8, max_tokens=64, max_nodes=16, max_batch=8)
+    for i in range(8):
+        v.prefill(i, synth.context_tokens(shape.vocab, 9 + 5 * i, stream=300 + i))
+    for nodes in ([16] * 5 + [1], [16] * 7 + [1], [16] * 8):
+        drafts = [synth.context_tokens(shape.vocab, n, stream=400 + i) for i, n in enumerate(nodes)]
+        v.verify_batch(list(range(len(nodes))), drafts)
+        got = v.logits(sum(nodes))
+        single = []
+        for i, n in enumerate(nodes):
+            v.verify(i, drafts[i])
+            single.append(v.logits(n))
+        e = _rel(got, np.concatenate(single))
+        log(f"{shape.name} {sum(nodes)} rows: against singles {e:.2e}")
+        assert e <= REL
+        v.verify_batch(list(range(len(nodes))), drafts)
+        np.testing.assert_array_equal(v.logits(sum(nodes)), got)
     v.close()

@@ -1,10 +1,12 @@
-"""The host's block-shape rule for prompt projections, evaluated on the CPU: the sizes that test_gpu_prompt.py
-names reach the block shapes that it names, and together every shape a prompt of more than 128 rows can take."""
+"""The host's block-shape rules, evaluated on the CPU: the sizes that test_gpu_prompt.py and test_gpu_many_rows.py
+name reach the block shapes that they name, and together every shape that a prompt of more than 128 rows, or the
+Q/K/V and gate/up projections of a step of 6 to 8 row tiles, can take."""
 import os
 import subprocess
 
 import pytest
 
+from tests import test_gpu_many_rows as many
 from tests.test_gpu_prompt import BLOCK_CASES, WIDE, WIDE_MAX_TOKENS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -52,3 +54,15 @@ def test_the_cases_cover_every_large_block():
         assert {c[i][:2] for c in BLOCK_CASES} == large
     assert {c[i][:2] for c in BLOCK_CASES for i in (4, 5)} == resid
     assert {c[i][2] for c in BLOCK_CASES for i in (4, 5)} == {1, 2, 3, 4}  # K splits
+
+
+def test_step_models_reach_every_block(rule):
+    seen = set()
+    for shape, q, g in [(many.SMALL, 2, 4), (many.SPLIT, 2, 4)] + list(many.WIDE.values()):
+        d, f = shape.d_model, shape.ffn_dim
+        for rt, mr in ((6, 6), (7, 8), (8, 8)):
+            got = rule("step", [(QKV, rt, 3 * d // 16, d // 32, 0), (SWIGLU, rt, 2 * f // 16, d // 32, 0)])
+            assert got == [(mr, q, 1), (mr, g, 1)], (shape.name, rt)
+            seen |= {(QKV,) + got[0][:2], (SWIGLU,) + got[1][:2]}
+    assert seen == {(QKV, m, n) for m in (6, 8) for n in (2, 3, 4, 6)} | {(SWIGLU, m, n) for m in (6, 8)
+                                                                          for n in (4, 6, 8, 10)}
