@@ -122,15 +122,18 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
   // an activation or weight tile, or one half of the alternating chunks of a
   // gate/up pair (KiB r of a pair: chunk r / 2).  Tiles past the matrix
   // re-read its last tile, whose outputs are not stored.  Where W does not
-  // divide the tiles, the last waves issue one tile less (`full`) and count
-  // their waits by it: loading the last tile again instead fetched its
-  // nontemporal weights again too (7B down of 48 rows 29.5 us, now 21.7).
+  // divide the tiles, the last waves load the last tile again, from the caches,
+  // in a prompt; in a step, where that fetched nontemporal weights again (7B
+  // down of 48 rows 29.5 us, now 21.7), they issue one tile less (`full`) and
+  // count their waits by it.
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)ring;
   const unsigned lane16 = lane * 16;
   const uint8_t* src[PT];
   bool pair[PT];   // gate/up weights: which half of the pair
   int half[PT];
-  const bool full = TT % W == 0 || wave < TT % W;  // this wave loads PT tiles a stage, else PT - 1
+  constexpr bool FEWER = !PRE && TT % W != 0;
+  const bool full = !FEWER || wave < TT % W;  // this wave loads PT tiles a stage, else PT - 1
+  const bool w_nt = !PRE && a.w_nt;
 #pragma unroll
   for (int i = 0; i < PT; ++i) {
     const int tl = min(wave + i * W, TT - 1);
@@ -144,17 +147,16 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
       src[i] = a.w + (size_t)min(ct0 + tl - MR, ct_all - 1) * nkc * kTileBytes;
   }
   // Loads of stage st into slot; chunks past the range re-read its last one.
-  // A step reads each weight tile once, so its weights are nontemporal, as in
-  // k_gemm, and do not push the K/V of the contexts out of the memory-side cache
-  // between steps: the attention of eight 1000-token contexts of the 7B shape
-  // takes 23.2 us a launch, 27.4 with ordinary weight loads (13B, four: 16.5 and
-  // 20.1).  A prompt's row blocks share the weights through L2.
+  // A step reads each weight tile once; where the model's weights do not fit
+  // the memory-side cache they are nontemporal, as in k_gemm, and do not push
+  // the K/V of the contexts out of it between steps (tile_weights_nt).  A
+  // prompt's row blocks share the weights through L2.
   auto issue = [&](int st, int slot) {
     const int c0 = c_lo + st * KCH;
 #pragma unroll
     for (int i = 0; i < PT; ++i) {
-      if (i == PT - 1 && !full) break;
-      const int tl = wave + i * W;
+      if (FEWER && i == PT - 1 && !full) break;
+      const int tl = min(wave + i * W, TT - 1);
       const unsigned dst = lds0 + (unsigned)(slot * U + tl * KCH) * 1024u;
       auto load = [&](auto nt) {
 #pragma unroll
@@ -164,7 +166,7 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
           dma_kib<nt>(src[i], lane16 + (unsigned)kib * 1024u, dst + s * 1024u);
         }
       };
-      if (!PRE && tl >= MR)
+      if (!PRE && w_nt && tl >= MR)
         load(std::true_type{});
       else
         load(std::false_type{});
@@ -267,12 +269,14 @@ __global__ __launch_bounds__(WM* WN * 64, WM * WN <= 4 && ST * (MR + NC) * KCH <
   // k + ST - 1 have been requested) and the others' are (the barrier), which
   // also says that every wave has read stage k out of `slot`.
   auto arrive = [&](int k) {
-    if (k + ST - 1 >= n_st)
+    if (k + ST - 1 < n_st) {
+      if (full)
+        wait_ring<(ST - 2) * PW>();
+      else
+        wait_ring<(ST - 2) * (PW - KCH)>();
+    } else {
       wait_ring<0>();
-    else if (full)
-      wait_ring<(ST - 2) * PW>();
-    else
-      wait_ring<(ST - 2) * (PW - KCH)>();
+    }
     barrier();
   };
   auto next = [&](int slot) { return slot + 1 == ST ? 0 : slot + 1; };

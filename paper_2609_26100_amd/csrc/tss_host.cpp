@@ -896,6 +896,7 @@ int enqueue_step(tss_ctx* c, bool verify, hipStream_t s, int start_layer = 0, co
     if (step_tiled(c->bf16, epi, mt, a.N)) {
       const TileShape t = step_tile(epi, mt, a.N / 16, a.nkc, c->wsl.kpart_bytes);
       a.ksplit = t.ks;
+      a.w_nt = tile_weights_nt(mt, L, d, f, cf.vocab);
       return launch_tile_step(epi, t, a, s);
     }
     a.ksplit = gemm_ksplit(epi, mt, a.N, a.nkc);

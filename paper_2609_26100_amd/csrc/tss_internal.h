@@ -230,9 +230,12 @@ struct alignas(64) GemmArgs {
   // its share of K; the ksplit partial products of a strip meet in kpart
   // (agent-scope accesses) and the last workgroup to arrive finishes the strip
   int ksplit;
-  // gate/up in blocks of two widths (gemm_wide_wgs > 0): workgroups
-  // [0, wide_wgs) take NT / 2 pairs, the rest NT / 2 - 1
-  int wide_wgs;
+  union {
+    // k_gemm's gate/up in blocks of two widths (gemm_wide_wgs > 0): workgroups
+    // [0, wide_wgs) take NT / 2 pairs, the rest NT / 2 - 1
+    int wide_wgs;
+    int w_nt;              // k_tile in a step: nontemporal weight loads (tile_weights_nt)
+  };
   int norm_dim;
   float eps;
   int pre_n0;              // prompt rows (k_tile): position and KV slot of row 0
@@ -580,6 +583,22 @@ inline bool step_tiled(bool bf16, int epi, int rt, int N) {
   if (rt >= 6) return true;
   if (epi == EPI_RESID) return (N + 63) / 64 * 3 <= kGemmRound;
   return rt == 5 && (epi == EPI_LOGITS || (epi == EPI_SWIGLU && gemm_wide_pairs(epi, rt, N) == 0));
+}
+
+// Whether a step's k_tile launches load their weights nontemporal.  What they
+// load with ordinary loads stays in the memory-side cache (256 MB) from step to
+// step where it fits, and where it does not it pushes the K/V out.  So the
+// weights that k_tile reads in a step (the residual projections' alone up to 4
+// row tiles, as good as all from 5 on) are kept while they take at most three
+// quarters of it.  12 blocks of d 512 (6 MB each), 17 rows: 456 us a step with
+// ordinary loads, 485 nontemporal.  7B shape, 12 blocks, 61 rows behind 1000
+// tokens: 1581 and 1546 us; two blocks of it, eight contexts of 1000 tokens:
+// attention 27.4 and 23.2 us a launch.
+constexpr size_t kKeptWeights = (size_t)192 << 20;
+inline bool tile_weights_nt(int rt, int n_layers, int d, int f, int vocab) {
+  const size_t resid = (size_t)n_layers * 2 * ((size_t)d * d + (size_t)d * f);
+  const size_t all = resid + (size_t)n_layers * 2 * (3 * (size_t)d * d + 2 * (size_t)d * f) + 2 * (size_t)vocab * d;
+  return (rt <= 4 ? resid : all) > kKeptWeights;
 }
 
 // Block shape of a step projection that k_tile runs.  The two-column Q/K/V and

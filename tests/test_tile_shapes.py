@@ -66,3 +66,16 @@ def test_step_models_reach_every_block(rule):
             seen |= {(QKV,) + got[0][:2], (SWIGLU,) + got[1][:2]}
     assert seen == {(QKV, m, n) for m in (6, 8) for n in (2, 3, 4, 6)} | {(SWIGLU, m, n) for m in (6, 8)
                                                                           for n in (4, 6, 8, 10)}
+
+
+def test_weights_are_nontemporal_where_they_do_not_fit_the_cache(rule):
+    """192 MiB of what k_tile reads in a step: O and down up to 4 row tiles, every projection from 5 on."""
+    mib = 1 << 20
+    models = [(4, 256, 704, 4096), (12, 512, 1408, 4096), (16, 1024, 2816, 32000), (2, 2048, 5632, 32000),
+              (16, 2048, 5632, 32000), (2, 4096, 11008, 32000), (32, 4096, 11008, 32000), (60, 6656, 17920, 32000),
+              (12, 2048, 2048, 32), (13, 2048, 2048, 32)]
+    for L, d, f, v in models:
+        resid = 2 * L * (d * d + d * f)
+        every = resid + 2 * L * (3 * d * d + 2 * d * f) + 2 * v * d
+        got = rule("nt", [(rt, L, d, f, v) for rt in (2, 4, 5, 8)])
+        assert got == [(int(x > 192 * mib),) for x in (resid, resid, every, every)], (L, d, f, v)
