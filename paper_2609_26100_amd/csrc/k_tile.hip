@@ -36,7 +36,8 @@
 // and CU plus the activations' at 60, whatever the depth of the ring (6 to 16
 // stages), and loading waves of their own or weights and activations in
 // rings of different depths change it by less than the runs differ (gate/up
-// of 120 rows 44-49 us, Q/K/V 34-37).
+// of 120 rows 44-49 us, Q/K/V 34-37, measured before a step's weights were
+// loaded once and nontemporal: 44 and 34 since).
 #include "tss_internal.h"
 
 #include <type_traits>
